@@ -19,7 +19,8 @@ import subprocess
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 SOURCES = [os.path.join(HERE, "csrc", f) for f in ("mppi_kernels.hip", "mppi_api.hip")]
-HEADERS = [os.path.join(HERE, "csrc", "mppi_dev.hpp"), os.path.join(ROOT, "include", "mppi.h")]
+HEADERS = [os.path.join(HERE, "csrc", "mppi_dev.hpp"), os.path.join(HERE, "csrc", "mppi_path.hpp"),
+           os.path.join(ROOT, "include", "mppi.h")]
 LIB = os.path.join(HERE, "libmppi.so")
 LIB_SAN = os.path.join(HERE, "libmppi_san.so")
 ARCH = os.environ.get("MPPI_OFFLOAD_ARCH", "gfx950")

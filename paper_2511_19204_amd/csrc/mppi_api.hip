@@ -34,6 +34,8 @@ __global__ void rollout_kernel(const DevInst*, const int2*, int, int, const floa
 template <int G, int D, int LEG> __global__ void rollout_trace_kernel(const DevInst*, const int2*, int, int);
 template <int G, int D, int LEG>
 __global__ void rollout_persistent_kernel(const DevInst*, const int2*, int, unsigned int*, int, int);
+__global__ void path_kernel(const DevInst*, const int2*, const float*, const float*);
+__global__ void path_predict_kernel(const PredItem*, PredItem);
 template <int GC> __global__ void chain_kernel(const DevInst*, const int2*, int, int, int);
 template <int G, int D> __global__ void team_kernel(const DevInst*, const int2*, int, int);
 template <int G> __global__ void team_persistent_kernel(const DevInst*, const int2*, int, unsigned int*, int, int);
@@ -64,8 +66,11 @@ using namespace mppi;
 
 // A launch key selects the schedule: 0 < G <= 64 is the body schedule with G
 // lanes per rollout, -GC < 0 the chain schedule with GC lanes per rollout, and
-// kTeamKey + G the team schedule with G lanes per rollout.
+// kTeamKey + G the team schedule with G lanes per rollout.  Launches of the body
+// schedule at its default lane count take kPathKey (a quad of lanes per
+// root-to-leaf path, the same results) where choose_keys says so.
 constexpr int kTeamKey = 128;
+constexpr int kPathKey = 256;
 static int key_lanes(int key) { return key > kTeamKey ? key - kTeamKey : key > 0 ? key : -key; }
 
 // ---------------------------------------------------------------------------
@@ -91,6 +96,7 @@ struct mppi_model {
   DevModel host;
   DevModel* dev = nullptr;
   int device = 0;
+  int simds = 0;  // of the device
   int nq = 0, nv = 0;
 };
 
@@ -277,6 +283,93 @@ static void build_chain_tables(DevModel& M) {
 }
 
 // ---------------------------------------------------------------------------
+// path kernel tables: the root-to-leaf paths below the floating base
+// ---------------------------------------------------------------------------
+static void build_path_tables(DevModel& M) {
+  const int nb = M.nb, fb = M.fb;
+  M.path_ok = 0;
+  M.path_ee = -1;
+  for (int p = 0; p < kMaxPaths; ++p)
+    for (int i = 0; i < kMaxPath; ++i) {
+      M.path_body[p][i] = -1;
+      M.path_src[p][i] = 0xffffffffu;
+    }
+  if (nb <= fb) return;
+  // one path per leaf, leaves in body order
+  int np = 0, len = 0;
+  for (int b = fb; b < nb; ++b) {
+    if (M.n_child[b] > 0) continue;
+    if (np >= kMaxPaths) return;
+    std::vector<int> up;
+    for (int x = b; x >= fb; x = M.parent[x]) up.push_back(x);
+    if ((int)up.size() > kMaxPath) return;
+    len = std::max(len, (int)up.size());
+    for (int i = 0; i < (int)up.size(); ++i) M.path_body[np][i] = up[up.size() - 1 - i];
+    ++np;
+  }
+  std::vector<int> first(nb, -1);  // first path holding a body
+  for (int p = 0; p < np; ++p)
+    for (int i = 0; i < kMaxPath; ++i) {
+      const int b = M.path_body[p][i];
+      if (b < 0) continue;
+      if (first[b] < 0) {
+        first[b] = p;
+        M.path_owner[p][i] = 1;
+      }
+      if (b == M.ee_body) M.path_ee = i;
+      M.path_cmax[i] = std::max(M.path_cmax[i], M.c_count[b]);
+    }
+  for (int p = 0; p < np; ++p)
+    for (int i = 0; i < kMaxPath; ++i) {
+      const int b = M.path_body[p][i];
+      if (b < 0) continue;
+      if (M.n_child[b] > 4) return;
+      if (M.n_child[b] > 1) {
+        if (len <= 3) len = 4;  // (the kernel of paths up to three bodies takes no shared ones)
+        M.path_branch |= 1 << i;
+      }
+      for (int k = 0; k < M.n_child[b]; ++k) {
+        const int ch = M.child[b][k];
+        const bool own = i + 1 < kMaxPath && M.path_body[p][i + 1] == ch;
+        M.path_src[p][i] = (M.path_src[p][i] & ~(255u << (8 * k))) | ((uint32_t)(own ? p : first[ch]) << (8 * k));
+      }
+    }
+  if (fb) {
+    // the base's children in body order are brought by increasing paths
+    for (int k = 0; k < M.n_child[0]; ++k) M.path_base_mask |= 1 << first[M.child[0][k]];
+  }
+  for (int i = 0; i < kMaxPath; ++i)
+    if (M.path_cmax[i] > 15) return;  // (4 bits each in the kernel)
+  for (int p = 0; p < kMaxPaths; ++p)
+    for (int i = 0; i < kMaxPath; ++i)
+      for (int k = 0; k < 3; ++k) {
+        float* r = M.path_rows[p][i][k];
+        for (int x = 0; x < kPathRow; ++x) r[x] = 0.f;
+        const int b = M.path_body[p][i];
+        if (b < 0) {
+          r[k] = 1.f;
+          r[15] = 1.f;
+          continue;
+        }
+        for (int c = 0; c < 3; ++c) {
+          r[c] = M.P[b][3 * k + c];
+          r[3 + c] = M.P[b][9 + 3 * k + c];
+          r[6 + c] = M.P[b][18 + 3 * k + c];
+          r[9 + c] = M.p_tree[b][c];
+          r[12 + c] = M.axis_p[b][c];
+          r[16 + c] = M.com[b][c];
+        }
+        r[15] = M.arm[b - fb];
+        for (int x = 0; x < 6; ++x) r[19 + x] = M.Ic[b][x];
+        r[25] = M.mass[b];
+      }
+  M.n_paths = np;
+  M.path_len = len;
+  M.path_lanes = 4 * (np <= 1 ? 1 : np <= 2 ? 2 : np <= 4 ? 4 : 8);
+  M.path_ok = 1;
+}
+
+// ---------------------------------------------------------------------------
 // model
 // ---------------------------------------------------------------------------
 extern "C" mppi_status mppi_model_create(const mppi_model_desc* d, mppi_model** out) {
@@ -371,9 +464,13 @@ extern "C" mppi_status mppi_model_create(const mppi_model_desc* d, mppi_model** 
     M.c_count[b] = ci - M.c_begin[b];
   }
   build_chain_tables(M);
+  build_path_tables(M);
   m->nq = fb ? 7 + nu : nu;
   m->nv = fb ? 6 + nu : nu;
   hipError_t e1 = hipGetDevice(&m->device);
+  int cus = 0;
+  if (e1 == hipSuccess) e1 = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, m->device);
+  m->simds = 4 * cus;
   hipError_t e2 = e1 == hipSuccess ? hipMalloc(&m->dev, sizeof(DevModel)) : e1;
   hipError_t e3 = e2 == hipSuccess ? hipMemcpy(m->dev, &M, sizeof(DevModel), hipMemcpyHostToDevice) : e2;
   if (e3 != hipSuccess) {
@@ -696,10 +793,18 @@ static bool serial_chain(const DevModel& M) {
   return true;
 }
 
+// Path kernels: rollouts and LDS bytes of a block (a wavefront).
+static int path_rollouts(const DevModel& M) { return M.path_ok ? 64 / M.path_lanes : 1; }
+static int path_len_of_kernel(const DevModel& M) { return M.path_len > 3 ? kMaxPath : 3; }
+static int path_block_bytes(const DevModel& M, int E) {
+  return (path_table_floats(M.nc, M.n_paths, path_len_of_kernel(M)) + path_rollouts(M) * path_group_floats(M.nb, E)) *
+         (int)sizeof(float);
+}
 struct Dims {
   int E = 0, nb = 0, nc = 0, nch = 0, natt = 0, ns = 0, depth = 0;
   // every instance added is a legged tree / of four chains of three / a serial chain
   bool leg = true, quad = true, serial = true;
+  int path_lds = 0;  // bytes of a block of the path kernels
   void add(const mppi_ctx* c) {
     const DevModel& M = c->m->host;
     leg = leg && legged(M);
@@ -712,6 +817,7 @@ struct Dims {
     natt = std::max(natt, M.n_att);
     ns = std::max(ns, M.team_slots);
     depth = std::max(depth, M.max_depth);
+    path_lds = std::max(path_lds, path_block_bytes(M, c->E));
   }
 };
 static Dims dims_of(const mppi_ctx* c) {
@@ -728,7 +834,9 @@ struct LaunchShape {
 };
 static LaunchShape launch_shape(int key, const Dims& dm) {
   LaunchShape sh;
-  if (key > kTeamKey) {
+  if (key >= kPathKey) {  // (rollouts per block and LDS layout are each instance's own)
+    sh.lds = dm.path_lds;
+  } else if (key > kTeamKey) {
     const int G = key - kTeamKey;
     sh.stride = team_layout(G, dm.ns, dm.E, dm.nch).total;
     sh.table = team_table_floats(dm.ns, dm.nc);
@@ -749,7 +857,70 @@ static LaunchShape launch_shape(int key, const Dims& dm) {
   }
   return sh;
 }
-static int rollouts_per_block(int key, const Dims& dm) { return launch_shape(key, dm).groups; }
+// rollouts of instance c per block of a launch over instances with dimensions dm
+static int rollouts_per_block(int key, const Dims& dm, const mppi_ctx* c) {
+  if (key == kPathKey) return path_rollouts(c->m->host);
+  return launch_shape(key, dm).groups;
+}
+
+// Whether the path kernels take an instance: its tree fits them, its knots fit a
+// block's LDS, and its end-effector cost (if it has one) is a path body's.
+constexpr int kPathLds = 64 * 1024;
+static bool path_fits(const mppi_ctx* c) {
+  const DevModel& M = c->m->host;
+  if (!M.path_ok || (M.fb && c->p.cost_kind == 0 && M.ee_body == 0)) return false;
+  return path_block_bytes(M, c->E) <= kPathLds;
+}
+
+// The keys the instances of one launch run with.  The path kernel serves the body
+// schedule at its default lane count while all its wavefronts of the launch are
+// resident at once (it takes a SIMD's whole register file): a quadruped's launch
+// at K = 4096 (1024 wavefronts) takes 0.65 instead of 0.74 ms, at K = 6144 (a
+// second turn of the SIMDs) as long as the body schedule's kernel, which runs
+// two wavefronts per SIMD; a hexapod's at 2048 / 4096 samples 0.24 instead of
+// 0.30 / 0.45 instead of 0.40 ms per 60 steps.
+static std::vector<int> choose_keys(const std::vector<const mppi_ctx*>& list) {
+  std::vector<int> keys(list.size());
+  long waves = 0;
+  std::vector<char> fits(list.size());
+  for (size_t i = 0; i < list.size(); ++i) {
+    const mppi_ctx* c = list[i];
+    keys[i] = c->lanes;
+    fits[i] = c->lanes == next_pow2(c->m->host.nb) && path_fits(c);
+    if (fits[i]) waves += (c->N + path_rollouts(c->m->host) - 1) / path_rollouts(c->m->host);
+  }
+  for (size_t i = 0; i < list.size(); ++i)
+    if (fits[i] && waves <= list[i]->m->simds) keys[i] = kPathKey;
+  return keys;
+}
+// Instances (indices into list) by key.  The persistent form keeps the chosen
+// schedules' own kernels.
+static std::map<int, std::vector<int>> group_by_key(const std::vector<const mppi_ctx*>& list, bool persistent) {
+  std::vector<int> keys;
+  if (persistent)
+    for (const mppi_ctx* c : list) keys.push_back(c->lanes);
+  else
+    keys = choose_keys(list);
+  std::map<int, std::vector<int>> by;
+  for (int a = 0; a < (int)list.size(); ++a) by[keys[a]].push_back(a);
+  return by;
+}
+// Work items (index into list, first sample) of a launch over the instances
+// `members` of list, the longest rollouts first.
+static std::vector<int2> work_table(int key, const Dims& dm, const std::vector<const mppi_ctx*>& list,
+                                    const std::vector<int>& members) {
+  std::vector<int> order = members;
+  std::stable_sort(order.begin(), order.end(), [&](int x, int y) {
+    const mppi_ctx *cx = list[x], *cy = list[y];
+    return (long)cx->H * cx->m->host.nsub * cx->m->host.nb > (long)cy->H * cy->m->host.nsub * cy->m->host.nb;
+  });
+  std::vector<int2> work;
+  for (int a : order) {
+    const int R = rollouts_per_block(key, dm, list[a]);
+    for (int n0 = 0; n0 < list[a]->N; n0 += R) work.push_back(make_int2(a, n0));
+  }
+  return work;
+}
 
 // the body schedule's kernel for trees at most 3 or 6 levels deep has its level
 // loops unrolled; deeper trees take the general one
@@ -811,8 +982,12 @@ static hipError_t launch_chain_GC(int blocks, const DevInst* insts, const int2* 
 // use instead of the instance's staged copies.
 static hipError_t launch_rollout(int key, int blocks, const DevInst* insts, const int2* work, const Dims& dm,
                                  hipStream_t s, const float* x0_in = nullptr, const float* nominal_in = nullptr) {
-  if ((x0_in || nominal_in) && !(key > 0 && key < kTeamKey)) return hipErrorInvalidValue;
+  if ((x0_in || nominal_in) && !(key > 0 && key < kTeamKey) && key < kPathKey) return hipErrorInvalidValue;
   const LaunchShape sh = launch_shape(key, dm);
+  if (key >= kPathKey) {
+    hipLaunchKernelGGL(path_kernel, dim3(blocks), dim3(64), sh.lds, s, insts, work, x0_in, nominal_in);
+    return hipGetLastError();
+  }
   switch (key) {
     case 4: return launch_rollout_G<4>(blocks, insts, work, sh, dm, s, x0_in, nominal_in);
     case 8: return launch_rollout_G<8>(blocks, insts, work, sh, dm, s, x0_in, nominal_in);
@@ -940,7 +1115,8 @@ static mppi_status run_iterations(mppi_ctx* c, float* d_knots_out, float* d_best
                                   float* d_costs, hipStream_t s, const float* x0_in = nullptr,
                                   const float* nominal_in = nullptr) {
   const Dims dm = dims_of(c);
-  const int R = rollouts_per_block(c->lanes, dm);
+  const int key = choose_keys({c})[0];
+  const int R = rollouts_per_block(key, dm, c);
   const int blocks = (c->N + R - 1) / R;
   for (int it = 0; it < c->I; ++it) {
     // timing marks: the rollout runs between marks 0 and 1, the update between 1 and 2
@@ -953,7 +1129,7 @@ static mppi_status run_iterations(mppi_ctx* c, float* d_knots_out, float* d_best
       HIP_TRY(hipEventRecord(mk[0], s));
     }
     const float* nom0 = it == 0 ? nominal_in : nullptr;
-    HIP_TRY(launch_rollout(c->lanes, blocks, c->d_insts + it, nullptr, dm, s, x0_in, nom0));
+    HIP_TRY(launch_rollout(key, blocks, c->d_insts + it, nullptr, dm, s, x0_in, nom0));
     if (c->profile) HIP_TRY(hipEventRecord(mk[1], s));
     UpdateOut o{nullptr, nullptr, nullptr, nom0};
     if (it == c->I - 1) o = UpdateOut{d_knots_out, d_best_knots, d_info, nom0};
@@ -995,6 +1171,12 @@ static hipError_t launch_predict_G(const mppi_ctx* c, int steps, float* out, hip
 // state_out <- state reached from c->x_meas along c->pred_knots after `steps` control steps
 static mppi_status launch_predict(const mppi_ctx* c, int steps, float* out, hipStream_t s) {
   hipError_t e;
+  if (path_fits(c)) {
+    hipLaunchKernelGGL(path_predict_kernel, dim3(1), dim3(64), path_block_bytes(c->m->host, c->E), s, nullptr,
+                       PredItem{c->d_pred_inst, out, steps});
+    HIP_TRY(hipGetLastError());
+    return MPPI_OK;
+  }
   switch (next_pow2(c->m->host.nb)) {
     case 4: e = launch_predict_G<4>(c, steps, out, s); break;
     case 8: e = launch_predict_G<8>(c, steps, out, s); break;
@@ -1089,6 +1271,7 @@ struct IterPlan {
 };
 struct Plan {
   std::vector<const mppi_ctx*> ctxs;
+  bool persistent = false;  // launch tables of the persistent form
   int device = 0;
   std::vector<IterPlan> iters;
   ~Plan() {
@@ -1127,9 +1310,10 @@ static void purge_plans(const mppi_ctx* c) {
                 g_plans.end());
 }
 
-static mppi_status build_plan(const std::vector<const mppi_ctx*>& ctxs, Plan** out) {
+static mppi_status build_plan(const std::vector<const mppi_ctx*>& ctxs, bool persistent, Plan** out) {
   auto plan = std::make_unique<Plan>();
   plan->ctxs = ctxs;
+  plan->persistent = persistent;
   HIP_TRY(hipGetDevice(&plan->device));
   int Imax = 0;
   for (auto* c : ctxs) Imax = std::max(Imax, c->I);
@@ -1150,25 +1334,14 @@ static mppi_status build_plan(const std::vector<const mppi_ctx*>& ctxs, Plan** o
     HIP_TRY(hipMemcpy(ip.insts, hi.data(), hi.size() * sizeof(DevInst), hipMemcpyHostToDevice));
     HIP_TRY(hipMalloc(&ip.ups, hu.size() * sizeof(DevUpdate)));
     HIP_TRY(hipMemcpy(ip.ups, hu.data(), hu.size() * sizeof(DevUpdate), hipMemcpyHostToDevice));
-    // one launch per lane count; inside it the longest rollouts first
-    std::map<int, std::vector<int>> byG;
-    for (int a = 0; a < (int)ip.active.size(); ++a) byG[ctxs[ip.active[a]]->lanes].push_back(a);
-    for (auto& kv : byG) {
+    // one launch per key; inside it the longest rollouts first
+    std::vector<const mppi_ctx*> list;
+    for (int i : ip.active) list.push_back(ctxs[i]);
+    for (auto& kv : group_by_key(list, persistent)) {
       GroupLaunch gl;
       gl.G = kv.first;
-      for (int a : kv.second) gl.dims.add(ctxs[ip.active[a]]);
-      const int R = rollouts_per_block(gl.G, gl.dims);
-      std::vector<int> order = kv.second;
-      std::stable_sort(order.begin(), order.end(), [&](int x, int y) {
-        const mppi_ctx* cx = ctxs[ip.active[x]];
-        const mppi_ctx* cy = ctxs[ip.active[y]];
-        return (long)cx->H * cx->m->host.nsub * cx->m->host.nb > (long)cy->H * cy->m->host.nsub * cy->m->host.nb;
-      });
-      std::vector<int2> work;
-      for (int a : order) {
-        const mppi_ctx* c = ctxs[ip.active[a]];
-        for (int n0 = 0; n0 < c->N; n0 += R) work.push_back(make_int2(a, n0));
-      }
+      for (int a : kv.second) gl.dims.add(list[a]);
+      const std::vector<int2> work = work_table(gl.G, gl.dims, list, kv.second);
       gl.blocks = (int)work.size();
       HIP_TRY(hipMalloc(&gl.counter, sizeof(unsigned int)));
       HIP_TRY(hipMalloc(&gl.work, work.size() * sizeof(int2)));
@@ -1234,11 +1407,12 @@ extern "C" mppi_status mppi_step_batch(int32_t n, mppi_ctx* const* ctxs, const f
   std::lock_guard<std::mutex> lk(g_mu);
   Plan* plan = nullptr;
   int dev = 0;
+  const bool persistent = g_persistent != 0;
   HIP_TRY(hipGetDevice(&dev));
   for (auto& p : g_plans)
-    if (p->ctxs == list && p->device == dev) { plan = p.get(); break; }
+    if (p->ctxs == list && p->device == dev && p->persistent == persistent) { plan = p.get(); break; }
   if (!plan) {
-    mppi_status st = build_plan(list, &plan);
+    mppi_status st = build_plan(list, persistent, &plan);
     if (st != MPPI_OK) return st;
   }
   // per-call block: stage items [2n], then per-iteration output tables
@@ -1277,7 +1451,7 @@ extern "C" mppi_status mppi_step_batch(int32_t n, mppi_ctx* const* ctxs, const f
   for (int it = 0; it < Imax; ++it) {
     IterPlan& ip = plan->iters[it];
     for (auto& g : ip.groups) {
-      if (g_persistent)
+      if (persistent)
         HIP_TRY(launch_persistent(g.G, g.blocks, ip.insts, g.work, g.dims, g.counter, s));
       else
         HIP_TRY(launch_rollout(g.G, g.blocks, ip.insts, g.work, g.dims, s));
@@ -1316,7 +1490,8 @@ extern "C" mppi_status mppi_graph_create(int32_t n, mppi_ctx* const* ctxs, const
   std::lock_guard<std::mutex> lk(g_mu);
   // a graph owns its own plan (not the shared cache, which may evict)
   Plan* plan = nullptr;
-  mppi_status st = build_plan(list, &plan);
+  const bool persistent = g_persistent != 0;
+  mppi_status st = build_plan(list, persistent, &plan);
   if (st != MPPI_OK) return st;
   auto owned = std::move(g_plans.back());
   g_plans.pop_back();
@@ -1355,7 +1530,7 @@ extern "C" mppi_status mppi_graph_create(int32_t n, mppi_ctx* const* ctxs, const
     for (int it = 0; it < Imax && e == hipSuccess; ++it) {
       IterPlan& ip = plan->iters[it];
       for (auto& gl : ip.groups) {
-        e = g_persistent ? launch_persistent(gl.G, gl.blocks, ip.insts, gl.work, gl.dims, gl.counter, cs)
+        e = persistent ? launch_persistent(gl.G, gl.blocks, ip.insts, gl.work, gl.dims, gl.counter, cs)
                          : launch_rollout(gl.G, gl.blocks, ip.insts, gl.work, gl.dims, cs);
         if (e != hipSuccess) break;
       }
@@ -1567,7 +1742,7 @@ extern "C" mppi_status mppi_debug_rollouts(mppi_ctx* c, const float* d_state, co
   DevInst* d = nullptr;
   mppi_status st = debug_inst(h, s, &d);
   if (st != MPPI_OK) return st;
-  const int R = rollouts_per_block(c->lanes, dims_of(c));
+  const int R = rollouts_per_block(c->lanes, dims_of(c), c);
   HIP_TRY(launch_rollout(c->lanes, (c->N + R - 1) / R, d, nullptr, dims_of(c), s));
   HIP_TRY(hipStreamSynchronize(s));
   HIP_TRY(hipFree(d));
@@ -1802,14 +1977,20 @@ struct BatchReq {
   int32_t n_it = -1;
 };
 
-// Prediction groups of a batch's ticks by lane count: the launch shape covers the
-// largest instance of the group.
-static int pred_lanes(const mppi_ctx* c) {
+// Prediction groups of a batch's ticks by kernel (the path kernel, or the body
+// schedule's by lane count): the launch shape covers the largest instance of the
+// group.
+static int pred_key(const mppi_ctx* c) {
+  if (path_fits(c)) return kPathKey;
   const int g = next_pow2(c->m->host.nb);
   return g < 4 ? 4 : (g > 64 ? 64 : g);
 }
-static hipError_t launch_predict_batch(int G, int n_items, const PredItem* items, int stride, int table,
-                                       hipStream_t s) {
+static hipError_t launch_predict_batch(int G, int n_items, const PredItem* items, const Dims& dm, hipStream_t s) {
+  if (G == kPathKey) {
+    hipLaunchKernelGGL(path_predict_kernel, dim3(n_items), dim3(64), dm.path_lds, s, items, PredItem{});
+    return hipGetLastError();
+  }
+  const int stride = group_floats(G, dm.E), table = body_sched_table_floats(dm.nb, dm.nc);
   const int lds = (table + (64 / G) * stride) * (int)sizeof(float);
   switch (G) {
     case 4: hipLaunchKernelGGL(predict_batch_kernel<4>, dim3(n_items), dim3(64), lds, s, items, stride, table); break;
@@ -1845,7 +2026,7 @@ static mppi_status launch_batch_dynamic(const std::vector<BatchReq>& reqs, unsig
     n_iters[i] = reqs[i].n_it < 0 ? left : std::min(reqs[i].n_it, left);
     Imax = std::max(Imax, n_iters[i]);
   }
-  struct GroupDesc { int G; Dims dims; size_t work_off; int n_items; };
+  struct GroupDesc { int G; Dims dims; size_t work_off; std::vector<int2> work; };
   // upd: the update launches' grids (the active list holds the 64-thread
   // updates first); blocks beyond an instance's own parts return at once but
   // would still wait for a free slot on a busy device
@@ -1861,7 +2042,7 @@ static mppi_status launch_batch_dynamic(const std::vector<BatchReq>& reqs, unsig
     staged.push_back(i);
     if (reqs[i].tick) {
       ticks.push_back(i);
-      pred_groups[pred_lanes(reqs[i].ctx)].push_back(i);
+      pred_groups[pred_key(reqs[i].ctx)].push_back(i);
     }
   }
   const int ns = (int)staged.size(), nt = (int)ticks.size();
@@ -1885,15 +2066,14 @@ static mppi_status launch_batch_dynamic(const std::vector<BatchReq>& reqs, unsig
     d.inst_off = bytes; bytes = align(bytes + d.n_active * sizeof(DevInst));
     d.up_off = bytes; bytes = align(bytes + d.n_active * sizeof(DevUpdate));
     d.out_off = bytes; bytes = align(bytes + d.n_active * sizeof(UpdateOut));
-    std::map<int, std::vector<int>> byG;
-    for (int a = 0; a < d.n_active; ++a) byG[reqs[active[it][a]].ctx->lanes].push_back(a);
-    for (auto& kv : byG) {
-      GroupDesc g{kv.first, Dims{}, bytes, 0};
-      for (int a : kv.second) g.dims.add(reqs[active[it][a]].ctx);
-      const int R = rollouts_per_block(g.G, g.dims);
-      for (int a : kv.second) g.n_items += (reqs[active[it][a]].ctx->N + R - 1) / R;
-      bytes = align(bytes + g.n_items * sizeof(int2));
-      d.groups.push_back(g);
+    std::vector<const mppi_ctx*> list;
+    for (int i : active[it]) list.push_back(reqs[i].ctx);
+    for (auto& kv : group_by_key(list, persistent)) {
+      GroupDesc g{kv.first, Dims{}, bytes, {}};
+      for (int a : kv.second) g.dims.add(list[a]);
+      g.work = work_table(g.G, g.dims, list, kv.second);
+      bytes = align(bytes + g.work.size() * sizeof(int2));
+      d.groups.push_back(std::move(g));
     }
   }
   RingSlot* r = nullptr;
@@ -1943,23 +2123,7 @@ static mppi_status launch_batch_dynamic(const std::vector<BatchReq>& reqs, unsig
       d.upd.add(hu[a]);
       ho[a] = q.ctx->I - 1 == ci ? UpdateOut{q.knots_out, q.best_out, q.info_out} : UpdateOut{nullptr, nullptr, nullptr};
     }
-    std::map<int, std::vector<int>> byG;
-    for (int a = 0; a < d.n_active; ++a) byG[reqs[active[it][a]].ctx->lanes].push_back(a);
-    size_t gi = 0;
-    for (auto& kv : byG) {
-      GroupDesc& g = d.groups[gi++];
-      const int R = rollouts_per_block(g.G, g.dims);
-      std::vector<int> order = kv.second;
-      std::stable_sort(order.begin(), order.end(), [&](int x, int y) {
-        const mppi_ctx* cx = reqs[active[it][x]].ctx;
-        const mppi_ctx* cy = reqs[active[it][y]].ctx;
-        return (long)cx->H * cx->m->host.nsub * cx->m->host.nb > (long)cy->H * cy->m->host.nsub * cy->m->host.nb;
-      });
-      auto* w = reinterpret_cast<int2*>(h + g.work_off);
-      int k = 0;
-      for (int a : order)
-        for (int n0 = 0; n0 < reqs[active[it][a]].ctx->N; n0 += R) w[k++] = make_int2(a, n0);
-    }
+    for (const GroupDesc& g : d.groups) std::copy(g.work.begin(), g.work.end(), reinterpret_cast<int2*>(h + g.work_off));
   }
   r->pending = true;  // event recorded after the last kernel reading the tables
   if (ns > 0) {
@@ -1969,14 +2133,10 @@ static mppi_status launch_batch_dynamic(const std::vector<BatchReq>& reqs, unsig
   if (nt > 0) {
     int k = 0;
     for (auto& kv : pred_groups) {
-      int stride = 0, table = 0;
-      for (int i : kv.second) {
-        const mppi_ctx* c = reqs[i].ctx;
-        stride = std::max(stride, group_floats(kv.first, c->E));
-        table = std::max(table, body_sched_table_floats(c->m->host.nb, c->nc));
-      }
+      Dims dm;
+      for (int i : kv.second) dm.add(reqs[i].ctx);
       HIP_TRY(launch_predict_batch(kv.first, (int)kv.second.size(), reinterpret_cast<const PredItem*>(dv + pred_off) + k,
-                                   stride, table, s));
+                                   dm, s));
       k += (int)kv.second.size();
     }
     hipLaunchKernelGGL(shift_batch_kernel, dim3(nt), dim3(kShiftThreads), 0, s, reinterpret_cast<const ShiftItem*>(dv + shift_off));
@@ -1997,9 +2157,9 @@ static mppi_status launch_batch_dynamic(const std::vector<BatchReq>& reqs, unsig
       const hipStream_t gs = (n_fork > 0 && k > 0) ? fork->aux[(k - 1) % n_fork] : s;
       auto* w = reinterpret_cast<const int2*>(dv + g.work_off);
       if (persistent && counters && ci < n_counters)
-        HIP_TRY(launch_persistent(g.G, g.n_items, di, w, g.dims, counters + ci++, gs));
+        HIP_TRY(launch_persistent(g.G, (int)g.work.size(), di, w, g.dims, counters + ci++, gs));
       else
-        HIP_TRY(launch_rollout(g.G, g.n_items, di, w, g.dims, gs));
+        HIP_TRY(launch_rollout(g.G, (int)g.work.size(), di, w, g.dims, gs));
     }
     for (int j = 0; j < n_fork; ++j) {
       HIP_TRY(hipEventRecord(fork->ev_join[j], fork->aux[j]));

@@ -14,6 +14,10 @@ constexpr int kMaxChains = 8;    // chain schedule: kinematic chains (lanes) per
 constexpr int kMaxLevels = 16;   // chain schedule: tree depth + 1
 constexpr int kRow = 68;         // floats per body row of the chain schedule's table
 constexpr int kCt = 8;           // floats per contact row of that table
+constexpr int kMaxPaths = 8;     // path kernels: root-to-leaf paths (quads of lanes) per rollout
+constexpr int kMaxPath = 6;      // path kernels: bodies of a path
+constexpr int kPathRow = 28;     // floats per path, body and coordinate lane of their constants
+constexpr int kPathExch = 20;    // floats per lane of their exchange records (14 used; staggers the banks)
 
 // Body row of the chain schedule's table (floats; integer fields stored as bits):
 //   [0,27) P   [27,30) p_tree   [30,33) axis_p   [33,36) com   [36,42) Ic   42 mass
@@ -84,6 +88,23 @@ struct DevModel {
   int32_t chain_parent[kMaxChains];             // parent body of its first body, or -1
   int32_t team_slot[kMaxBodies];                // rank of (depth, chain) among the bodies
   alignas(16) float team_rows[kMaxBodies][kTeamRow];
+  // Path kernels: the root-to-leaf paths of the tree (below the floating base),
+  // each on a quad of lanes (path_lanes per rollout); a body that several paths
+  // share belongs to each of them.
+  int32_t path_ok;                              // 1 if the tree fits the path kernels
+  int32_t n_paths, path_lanes, path_len;        // path_len: bodies of the longest path
+  int32_t path_branch;                          // bit i: a body at index i has children on several paths
+  int32_t path_base_mask;                       // bit p: path p brings one of the base's children
+  int32_t path_ee;                              // index of the end-effector body on its path, or -1
+  int32_t path_body[kMaxPaths][kMaxPath];       // body at index i of path p, or -1
+  int32_t path_owner[kMaxPaths][kMaxPath];      // 1 on the first path that holds the body
+  uint32_t path_src[kMaxPaths][kMaxPath];       // paths bringing the body's children, in child order, 8 bits each (255: none)
+  int32_t path_cmax[kMaxPath];                  // most contact points of a body at index i
+  // per path, body and coordinate lane k: rows k of P0, P1, P2, then p_tree,
+  // axis_p, armature, com, Ic, mass (two floats unused).  Past a path's end: an
+  // identity rotation, no mass, armature 1, so the body passes its parent's
+  // frame on and hands nothing back.
+  alignas(16) float path_rows[kMaxPaths][kMaxPath][3][kPathRow];
 };
 
 // Task targets of an instance's costs (Sec. IV-A), in a block of their own that
@@ -262,6 +283,14 @@ __host__ __device__ inline int chain_group_floats(int GC, int nb, int E, int nch
   const int r4 = (raw + 3) & ~3;
   return r4 + ((20 - r4 % 32) + 32) % 32;  // 16-byte aligned groups, staggered across LDS banks
 }
+
+// Path kernels: after the model table the constants of np paths of up to L
+// bodies (kPathRow floats per coordinate lane) and the exchange records of the
+// 64 lanes and one of zeros; per rollout group the knots and the costs by body.
+__host__ __device__ inline int path_table_floats(int nc, int np, int L) {
+  return body_table_floats(nc) + np * L * 3 * kPathRow + 65 * kPathExch;
+}
+__host__ __device__ inline int path_group_floats(int nb, int E) { return ((E + 3) & ~3) + ((nb + 3) & ~3); }
 
 // Team schedule: after the model table (then the team constants [slots][60] and
 // the slot of chain c's body at depth d [kMaxChains][kMaxLevels] as integer

@@ -257,6 +257,11 @@ template <int N>
 __device__ __forceinline__ float from_row_lane(float x) {
   return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, x), 0x100 + N, 0xf, 0xf, true));
 }
+// value held by another lane of this lane's quad (DPP quad permutation)
+template <int CTRL>
+__device__ __forceinline__ float qperm(float x) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, x), CTRL, 0xf, 0xf, true));
+}
 // value held by the first lane of this lane's rollout group of G lanes (groups
 // are aligned): for G = 16 a DPP broadcast of each row's lane 0
 // (row_newbcast:0), for G = 4 a quad permutation (0, 0, 0, 0), else a swizzle
@@ -1630,6 +1635,12 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void ro
   }
 }
 
+}  // namespace mppi
+
+#include "mppi_path.hpp"
+
+namespace mppi {
+
 // ---------------------------------------------------------------------------
 // Team schedule: every chain of the heavy-path decomposition owns a block of B
 // lanes (B = 4 or 8, holding the chain's bodies).  The per-body work runs one
@@ -1643,10 +1654,6 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void ro
 // Sums over the three lanes are taken in the order 0, 1, 2 in every lane, so the
 // lanes of a team agree bit for bit on every shared scalar.
 // ---------------------------------------------------------------------------
-template <int CTRL>
-__device__ __forceinline__ float qperm(float x) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, x), CTRL, 0xf, 0xf, true));
-}
 __device__ __forceinline__ float qr1(float x) { return qperm<0xC9>(x); }  // component k + 1 (quad_perm 1,2,0,3)
 __device__ __forceinline__ float qr2(float x) { return qperm<0xD2>(x); }  // component k + 2 (quad_perm 2,0,1,3)
 __device__ __forceinline__ float qsum3(float x) { return (qperm<0x00>(x) + qperm<0x55>(x)) + qperm<0xAA>(x); }
