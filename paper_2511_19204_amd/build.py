@@ -18,9 +18,9 @@ import subprocess
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
-SOURCES = [os.path.join(HERE, "csrc", f) for f in ("mppi_kernels.hip", "mppi_api.hip")]
-HEADERS = [os.path.join(HERE, "csrc", "mppi_dev.hpp"), os.path.join(HERE, "csrc", "mppi_path.hpp"),
-           os.path.join(ROOT, "include", "mppi.h")]
+SOURCES = [os.path.join(HERE, "csrc", f) for f in ("mppi_kernels.hip", "mppi_paths.hip", "mppi_api.hip")]
+HEADERS = [os.path.join(HERE, "csrc", f) for f in ("mppi_dev.hpp", "mppi_step.hpp", "mppi_path.hpp", "mppi_lane.hpp")]
+HEADERS.append(os.path.join(ROOT, "include", "mppi.h"))
 LIB = os.path.join(HERE, "libmppi.so")
 LIB_SAN = os.path.join(HERE, "libmppi_san.so")
 ARCH = os.environ.get("MPPI_OFFLOAD_ARCH", "gfx950")
@@ -87,16 +87,29 @@ def build(force: bool = True, verbose: bool = False, sanitize: bool = False) -> 
             return lib
     tmp = lib + ".tmp"
     extra = SAN_HOST if sanitize else []
-    cmd = ["hipcc", *FLAGS, *extra, "-Rpass-analysis=kernel-resource-usage", *SOURCES, "-o", tmp]
-    res = subprocess.run(cmd, capture_output=True, text=True)
+    flags = [f for f in FLAGS if f != "-shared"] + [f for f in extra if f != "-shared-libsan"]
+    # the sources side by side (minutes each), then linked
+    objs = [f"{tmp}.{os.path.splitext(os.path.basename(src))[0]}.o" for src in SOURCES]
+    procs = [subprocess.Popen(["hipcc", *flags, "-Rpass-analysis=kernel-resource-usage", "-c", src, "-o", obj],
+                              stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+             for src, obj in zip(SOURCES, objs)]
+    outs = [p.communicate()[0] for p in procs]
+    rc = [p.returncode for p in procs]
+    if not any(rc):
+        res = subprocess.run(["hipcc", *FLAGS, *extra, *objs, "-o", tmp], capture_output=True, text=True)
+        outs.append(res.stdout + res.stderr)
+        rc.append(res.returncode)
+    for obj in objs:
+        if os.path.exists(obj):
+            os.remove(obj)
     noise = ("packed-fp32-ops", "kernel-resource-usage")
-    msgs = [ln for ln in (res.stdout + res.stderr).splitlines()
+    msgs = [ln for ln in "\n".join(outs).splitlines()
             if not any(n in ln for n in noise) and ln.strip() and not ln.startswith(" ") and ln.strip() != "^"]
-    if res.returncode != 0:
+    if any(rc):
         raise RuntimeError("hipcc failed:\n" + "\n".join(msgs))
     if verbose and msgs:
         print("\n".join(msgs))
-    check_resources(resource_usage(res.stderr))
+    check_resources(resource_usage("\n".join(outs)))
     os.replace(tmp, lib)
     return lib
 

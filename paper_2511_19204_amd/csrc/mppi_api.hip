@@ -34,8 +34,8 @@ __global__ void rollout_kernel(const DevInst*, const int2*, int, int, const floa
 template <int G, int D, int LEG> __global__ void rollout_trace_kernel(const DevInst*, const int2*, int, int);
 template <int G, int D, int LEG>
 __global__ void rollout_persistent_kernel(const DevInst*, const int2*, int, unsigned int*, int, int);
-__global__ void path_kernel(const DevInst*, const int2*, const float*, const float*);
-__global__ void path_predict_kernel(const PredItem*, PredItem);
+// kernel (mppi_paths.hip)
+__global__ void path_kernel(const DevInst*, const int2*, int, const float*, const float*, const PredItem*, float*, int);
 template <int GC> __global__ void chain_kernel(const DevInst*, const int2*, int, int, int);
 template <int G, int D> __global__ void team_kernel(const DevInst*, const int2*, int, int);
 template <int G> __global__ void team_persistent_kernel(const DevInst*, const int2*, int, unsigned int*, int, int);
@@ -67,10 +67,12 @@ using namespace mppi;
 // A launch key selects the schedule: 0 < G <= 64 is the body schedule with G
 // lanes per rollout, -GC < 0 the chain schedule with GC lanes per rollout, and
 // kTeamKey + G the team schedule with G lanes per rollout.  Launches of the body
-// schedule at its default lane count take kPathKey (a quad of lanes per
-// root-to-leaf path, the same results) where choose_keys says so.
+// schedule at its default lane count take the path kernel (the same results) where
+// choose_keys says so: kPathKey with a quad of lanes per root-to-leaf path, kLaneKey
+// with one lane.
 constexpr int kTeamKey = 128;
 constexpr int kPathKey = 256;
+constexpr int kLaneKey = 257;
 static int key_lanes(int key) { return key > kTeamKey ? key - kTeamKey : key > 0 ? key : -key; }
 
 // ---------------------------------------------------------------------------
@@ -363,6 +365,29 @@ static void build_path_tables(DevModel& M) {
         for (int x = 0; x < 6; ++x) r[19 + x] = M.Ic[b][x];
         r[25] = M.mass[b];
       }
+  for (int p = 0; p < kMaxPaths; ++p)
+    for (int i = 0; i < kMaxPath; ++i) {
+      float* r = M.lane_rows[p][i];
+      for (int x = 0; x < kLaneRow; ++x) r[x] = 0.f;
+      const int b = M.path_body[p][i];
+      if (b < 0) {
+        r[0] = r[4] = r[8] = 1.f;
+        r[50] = 1.f;
+        continue;
+      }
+      for (int x = 0; x < 27; ++x) r[x] = M.P[b][x];
+      for (int x = 0; x < 3; ++x) {
+        r[28 + x] = M.p_tree[b][x];
+        r[31 + x] = M.axis_p[b][x];
+        r[40 + x] = M.com[b][x];
+      }
+      r[34] = M.kp[b - fb];
+      r[35] = M.kd[b - fb];
+      r[36] = M.taumax[b - fb];
+      for (int x = 0; x < 6; ++x) r[43 + x] = M.Ic[b][x];
+      r[49] = M.mass[b];
+      r[50] = M.arm[b - fb];
+    }
   M.n_paths = np;
   M.path_len = len;
   M.path_lanes = 4 * (np <= 1 ? 1 : np <= 2 ? 2 : np <= 4 ? 4 : 8);
@@ -795,16 +820,22 @@ static bool serial_chain(const DevModel& M) {
 
 // Path kernels: rollouts and LDS bytes of a block (a wavefront).
 static int path_rollouts(const DevModel& M) { return M.path_ok ? 64 / M.path_lanes : 1; }
-static int path_len_of_kernel(const DevModel& M) { return M.path_len > 3 ? kMaxPath : 3; }
+static int lane_rollouts(const DevModel& M) { return M.path_ok ? 256 / M.path_lanes : 1; }
+// bodies a path may have in the kernel variant that takes the tree
+static int path_len_of_kernel(const DevModel& M) { return M.path_len <= 3 ? 3 : M.path_len <= 4 ? 4 : kMaxPath; }
 static int path_block_bytes(const DevModel& M, int E) {
-  return (path_table_floats(M.nc, M.n_paths, path_len_of_kernel(M)) + path_rollouts(M) * path_group_floats(M.nb, E)) *
+  return (path_table_floats(M.nc, M.n_paths, path_len_of_kernel(M)) + path_rollouts(M) * path_group_floats(E)) *
+         (int)sizeof(float);
+}static int lane_block_bytes(const DevModel& M, int E) {
+  return (lane_table_floats(M.nc, M.n_paths, path_len_of_kernel(M)) + lane_rollouts(M) * path_group_floats(E)) *
          (int)sizeof(float);
 }
+
 struct Dims {
   int E = 0, nb = 0, nc = 0, nch = 0, natt = 0, ns = 0, depth = 0;
   // every instance added is a legged tree / of four chains of three / a serial chain
   bool leg = true, quad = true, serial = true;
-  int path_lds = 0;  // bytes of a block of the path kernels
+  int block_lds = 0;  // bytes of a block of the path kernel (launch_groups)
   void add(const mppi_ctx* c) {
     const DevModel& M = c->m->host;
     leg = leg && legged(M);
@@ -817,7 +848,6 @@ struct Dims {
     natt = std::max(natt, M.n_att);
     ns = std::max(ns, M.team_slots);
     depth = std::max(depth, M.max_depth);
-    path_lds = std::max(path_lds, path_block_bytes(M, c->E));
   }
 };
 static Dims dims_of(const mppi_ctx* c) {
@@ -835,7 +865,7 @@ struct LaunchShape {
 static LaunchShape launch_shape(int key, const Dims& dm) {
   LaunchShape sh;
   if (key >= kPathKey) {  // (rollouts per block and LDS layout are each instance's own)
-    sh.lds = dm.path_lds;
+    sh.lds = dm.block_lds;
   } else if (key > kTeamKey) {
     const int G = key - kTeamKey;
     sh.stride = team_layout(G, dm.ns, dm.E, dm.nch).total;
@@ -860,66 +890,135 @@ static LaunchShape launch_shape(int key, const Dims& dm) {
 // rollouts of instance c per block of a launch over instances with dimensions dm
 static int rollouts_per_block(int key, const Dims& dm, const mppi_ctx* c) {
   if (key == kPathKey) return path_rollouts(c->m->host);
+  if (key == kLaneKey) return lane_rollouts(c->m->host);
   return launch_shape(key, dm).groups;
 }
 
 // Whether the path kernels take an instance: its tree fits them, its knots fit a
 // block's LDS, and its end-effector cost (if it has one) is a path body's.
 constexpr int kPathLds = 64 * 1024;
+constexpr int kCuLds = 160 * 1024;  // of a compute unit
 static bool path_fits(const mppi_ctx* c) {
   const DevModel& M = c->m->host;
   if (!M.path_ok || (M.fb && c->p.cost_kind == 0 && M.ee_body == 0)) return false;
   return path_block_bytes(M, c->E) <= kPathLds;
 }
 
-// The keys the instances of one launch run with.  The path kernel serves the body
-// schedule at its default lane count while all its wavefronts of the launch are
-// resident at once (it takes a SIMD's whole register file): a quadruped's launch
-// at K = 4096 (1024 wavefronts) takes 0.65 instead of 0.74 ms, at K = 6144 (a
-// second turn of the SIMDs) as long as the body schedule's kernel, which runs
-// two wavefronts per SIMD; a hexapod's at 2048 / 4096 samples 0.24 instead of
-// 0.30 / 0.45 instead of 0.40 ms per 60 steps.
+// The keys the instances of one launch run with: kPathKey or kLaneKey (the path
+// kernel's two forms, which may share a launch) for the body schedule at its
+// default lane count where the tree fits them, else the chosen schedule.
+//
+// A SIMD holds one wavefront of either form.  The quad form's step is the
+// shorter (the one-lane form's takes 1.4 to 1.9 times as long: 3.4 and 5.4 us for
+// the quadruped, 7.4 and 12.2 for the humanoid, 2.0 and 3.4 for the arm), the
+// one-lane form needs a quarter of the wavefronts.  So while all quad-form
+// wavefronts are resident at once they are taken (quadruped, 4 096 samples x 60
+// steps: 0.25 ms, one-lane form 0.35, one lane per body 0.28); past that a second
+// turn of the SIMDs costs more than the longer step (6 144 samples: 0.44 / 0.37 /
+// 0.41; 16 384: 0.84 / 0.39 / 0.76; hexapod at 4 096: 0.50 / 0.38 / 0.44; humanoid
+// at 16 384: 1.73 / 0.81 / 2.55).  In a mixed launch that does not fit at once the
+// longest rollouts keep the quad form as far as that shortens the launch.
+constexpr double kLaneStep = 1.65;  // one-lane step over quad step
+// The quad form's time per rollout of an instance (microseconds: 0.65 a body of
+// the path, 1.3 the floating base, 0.4 a contact point).
+static double quad_time(const mppi_ctx* c) {
+  const DevModel& M = c->m->host;
+  double t = 0.65 * path_len_of_kernel(M) + 1.3 * M.fb;
+  for (int i = 0; i < kMaxPath; ++i) t += 0.4 * M.path_cmax[i];
+  return t * c->H * M.nsub;
+}
 static std::vector<int> choose_keys(const std::vector<const mppi_ctx*>& list) {
   std::vector<int> keys(list.size());
-  long waves = 0;
-  std::vector<char> fits(list.size());
-  for (size_t i = 0; i < list.size(); ++i) {
+  struct Cand {
+    int i;
+    double quad, quad_waves, lane_waves;  // time of a rollout in the quad form, wavefronts
+    int lane_lds;
+  };
+  std::vector<Cand> cand;
+  double waves = 0;
+  for (int i = 0; i < (int)list.size(); ++i) {
     const mppi_ctx* c = list[i];
+    const DevModel& M = c->m->host;
     keys[i] = c->lanes;
-    fits[i] = c->lanes == next_pow2(c->m->host.nb) && path_fits(c);
-    if (fits[i]) waves += (c->N + path_rollouts(c->m->host) - 1) / path_rollouts(c->m->host);
+    if (c->lanes != next_pow2(M.nb) || !path_fits(c)) continue;
+    keys[i] = kPathKey;
+    const int rp = path_rollouts(M), rl = lane_rollouts(M);
+    cand.push_back({i, quad_time(c), (double)((c->N + rp - 1) / rp), (double)((c->N + rl - 1) / rl),
+                    lane_block_bytes(M, c->E)});
+    waves += cand.back().quad_waves;
   }
-  for (size_t i = 0; i < list.size(); ++i)
-    if (fits[i] && waves <= list[i]->m->simds) keys[i] = kPathKey;
+  if (cand.empty() || waves <= list[cand[0].i]->m->simds) return keys;
+  const double simds = list[cand[0].i]->m->simds;
+  // the first k of the candidates, longest first, in the quad form, the rest in
+  // the one-lane form: the launch lasts about as long as its longest rollout or
+  // its work spread over the SIMDs, whichever is more (one instance: whole turns)
+  std::stable_sort(cand.begin(), cand.end(), [](const Cand& a, const Cand& b) { return a.quad > b.quad; });
+  const int n = (int)cand.size();
+  // the one-lane form keeps 64 / G rollouts' knots in a block's LDS: a mixed launch
+  // takes it where four blocks fit a compute unit, one instance also with fewer
+  auto lane_ok = [&](const Cand& c) { return c.lane_lds <= (n == 1 ? kPathLds : kCuLds / 4); };
+  const double lane_simds = n == 1 ? simds / 4 * std::min(4, kCuLds / cand[0].lane_lds) : simds;
+  int best_k = n;
+  double best = 1e300;
+  for (int k = n; k >= 0; --k) {
+    double longest = 0, work = 0;
+    for (int j = 0; j < n; ++j) {
+      const Cand& c = cand[j];
+      const bool lane = j >= k && lane_ok(c);
+      const double t = lane ? kLaneStep * c.quad : c.quad, w = lane ? c.lane_waves : c.quad_waves;
+      longest = std::max(longest, t);
+      work += t * (n == 1 ? std::ceil(w / (lane ? lane_simds : simds)) * simds : w);
+    }
+    const double est = n == 1 ? work / simds : std::max(longest, work / simds) + 0.2 * std::min(longest, work / simds);
+    if (est < best) {
+      best = est;
+      best_k = k;
+    }
+  }
+  for (int j = best_k; j < n; ++j)
+    if (lane_ok(cand[j])) keys[cand[j].i] = kLaneKey;
   return keys;
 }
-// Instances (indices into list) by key.  The persistent form keeps the chosen
-// schedules' own kernels.
-static std::map<int, std::vector<int>> group_by_key(const std::vector<const mppi_ctx*>& list, bool persistent) {
+// The launches of a list of instances: per launch the key (kPathKey for both
+// forms of the path kernel), its dimensions and its work table: (index into list,
+// first sample), with kLaneItem where the one-lane form runs an item, longest
+// rollouts first.  The persistent form keeps the chosen schedules' own kernels.
+struct LaunchGroup {
+  int key = 0;
+  Dims dims;
+  std::vector<int2> work;
+};
+static std::vector<LaunchGroup> launch_groups(const std::vector<const mppi_ctx*>& list, bool persistent) {
   std::vector<int> keys;
   if (persistent)
     for (const mppi_ctx* c : list) keys.push_back(c->lanes);
   else
     keys = choose_keys(list);
   std::map<int, std::vector<int>> by;
-  for (int a = 0; a < (int)list.size(); ++a) by[keys[a]].push_back(a);
-  return by;
-}
-// Work items (index into list, first sample) of a launch over the instances
-// `members` of list, the longest rollouts first.
-static std::vector<int2> work_table(int key, const Dims& dm, const std::vector<const mppi_ctx*>& list,
-                                    const std::vector<int>& members) {
-  std::vector<int> order = members;
-  std::stable_sort(order.begin(), order.end(), [&](int x, int y) {
-    const mppi_ctx *cx = list[x], *cy = list[y];
-    return (long)cx->H * cx->m->host.nsub * cx->m->host.nb > (long)cy->H * cy->m->host.nsub * cy->m->host.nb;
-  });
-  std::vector<int2> work;
-  for (int a : order) {
-    const int R = rollouts_per_block(key, dm, list[a]);
-    for (int n0 = 0; n0 < list[a]->N; n0 += R) work.push_back(make_int2(a, n0));
+  for (int a = 0; a < (int)list.size(); ++a) by[keys[a] == kLaneKey ? kPathKey : keys[a]].push_back(a);
+  std::vector<LaunchGroup> out;
+  for (auto& kv : by) {
+    LaunchGroup g;
+    g.key = kv.first;
+    for (int a : kv.second) {
+      g.dims.add(list[a]);
+      if (keys[a] == kLaneKey) g.dims.block_lds = std::max(g.dims.block_lds, lane_block_bytes(list[a]->m->host, list[a]->E));
+      if (keys[a] == kPathKey) g.dims.block_lds = std::max(g.dims.block_lds, path_block_bytes(list[a]->m->host, list[a]->E));
+    }
+    auto length = [&](int a) {
+      const DevModel& M = list[a]->m->host;
+      if (g.key != kPathKey) return (double)list[a]->H * M.nsub * M.nb;
+      return quad_time(list[a]) * (keys[a] == kLaneKey ? kLaneStep : 1.0);
+    };
+    std::stable_sort(kv.second.begin(), kv.second.end(), [&](int x, int y) { return length(x) > length(y); });
+    for (int a : kv.second) {
+      const int R = rollouts_per_block(keys[a], g.dims, list[a]);
+      const int form = keys[a] == kLaneKey ? kLaneItem : 0;
+      for (int n0 = 0; n0 < list[a]->N; n0 += R) g.work.push_back(make_int2(a, n0 | form));
+    }
+    out.push_back(std::move(g));
   }
-  return work;
+  return out;
 }
 
 // the body schedule's kernel for trees at most 3 or 6 levels deep has its level
@@ -985,7 +1084,8 @@ static hipError_t launch_rollout(int key, int blocks, const DevInst* insts, cons
   if ((x0_in || nominal_in) && !(key > 0 && key < kTeamKey) && key < kPathKey) return hipErrorInvalidValue;
   const LaunchShape sh = launch_shape(key, dm);
   if (key >= kPathKey) {
-    hipLaunchKernelGGL(path_kernel, dim3(blocks), dim3(64), sh.lds, s, insts, work, x0_in, nominal_in);
+    hipLaunchKernelGGL(path_kernel, dim3(blocks), dim3(64), sh.lds, s, insts, work, key == kLaneKey ? 1 : 0, x0_in,
+                       nominal_in, nullptr, nullptr, 0);
     return hipGetLastError();
   }
   switch (key) {
@@ -1114,8 +1214,9 @@ extern "C" mppi_status mppi_set_batch_options(const mppi_batch_opts* o) {
 static mppi_status run_iterations(mppi_ctx* c, float* d_knots_out, float* d_best_knots, mppi_step_info* d_info,
                                   float* d_costs, hipStream_t s, const float* x0_in = nullptr,
                                   const float* nominal_in = nullptr) {
-  const Dims dm = dims_of(c);
+  Dims dm = dims_of(c);
   const int key = choose_keys({c})[0];
+  dm.block_lds = key == kLaneKey ? lane_block_bytes(c->m->host, c->E) : path_block_bytes(c->m->host, c->E);
   const int R = rollouts_per_block(key, dm, c);
   const int blocks = (c->N + R - 1) / R;
   for (int it = 0; it < c->I; ++it) {
@@ -1172,8 +1273,8 @@ static hipError_t launch_predict_G(const mppi_ctx* c, int steps, float* out, hip
 static mppi_status launch_predict(const mppi_ctx* c, int steps, float* out, hipStream_t s) {
   hipError_t e;
   if (path_fits(c)) {
-    hipLaunchKernelGGL(path_predict_kernel, dim3(1), dim3(64), path_block_bytes(c->m->host, c->E), s, nullptr,
-                       PredItem{c->d_pred_inst, out, steps});
+    hipLaunchKernelGGL(path_kernel, dim3(1), dim3(64), path_block_bytes(c->m->host, c->E), s, c->d_pred_inst, nullptr, 0,
+                       nullptr, nullptr, nullptr, out, steps);
     HIP_TRY(hipGetLastError());
     return MPPI_OK;
   }
@@ -1337,15 +1438,14 @@ static mppi_status build_plan(const std::vector<const mppi_ctx*>& ctxs, bool per
     // one launch per key; inside it the longest rollouts first
     std::vector<const mppi_ctx*> list;
     for (int i : ip.active) list.push_back(ctxs[i]);
-    for (auto& kv : group_by_key(list, persistent)) {
+    for (const LaunchGroup& lg : launch_groups(list, persistent)) {
       GroupLaunch gl;
-      gl.G = kv.first;
-      for (int a : kv.second) gl.dims.add(list[a]);
-      const std::vector<int2> work = work_table(gl.G, gl.dims, list, kv.second);
-      gl.blocks = (int)work.size();
+      gl.G = lg.key;
+      gl.dims = lg.dims;
+      gl.blocks = (int)lg.work.size();
       HIP_TRY(hipMalloc(&gl.counter, sizeof(unsigned int)));
-      HIP_TRY(hipMalloc(&gl.work, work.size() * sizeof(int2)));
-      HIP_TRY(hipMemcpy(gl.work, work.data(), work.size() * sizeof(int2), hipMemcpyHostToDevice));
+      HIP_TRY(hipMalloc(&gl.work, lg.work.size() * sizeof(int2)));
+      HIP_TRY(hipMemcpy(gl.work, lg.work.data(), lg.work.size() * sizeof(int2), hipMemcpyHostToDevice));
       ip.groups.push_back(gl);
     }
   }
@@ -1987,7 +2087,9 @@ static int pred_key(const mppi_ctx* c) {
 }
 static hipError_t launch_predict_batch(int G, int n_items, const PredItem* items, const Dims& dm, hipStream_t s) {
   if (G == kPathKey) {
-    hipLaunchKernelGGL(path_predict_kernel, dim3(n_items), dim3(64), dm.path_lds, s, items, PredItem{});
+    const int lds = dm.block_lds;
+    hipLaunchKernelGGL(path_kernel, dim3(n_items), dim3(64), lds, s, nullptr, nullptr, 0, nullptr, nullptr, items,
+                       nullptr, 0);
     return hipGetLastError();
   }
   const int stride = group_floats(G, dm.E), table = body_sched_table_floats(dm.nb, dm.nc);
@@ -2068,10 +2170,8 @@ static mppi_status launch_batch_dynamic(const std::vector<BatchReq>& reqs, unsig
     d.out_off = bytes; bytes = align(bytes + d.n_active * sizeof(UpdateOut));
     std::vector<const mppi_ctx*> list;
     for (int i : active[it]) list.push_back(reqs[i].ctx);
-    for (auto& kv : group_by_key(list, persistent)) {
-      GroupDesc g{kv.first, Dims{}, bytes, {}};
-      for (int a : kv.second) g.dims.add(list[a]);
-      g.work = work_table(g.G, g.dims, list, kv.second);
+    for (LaunchGroup& lg : launch_groups(list, persistent)) {
+      GroupDesc g{lg.key, lg.dims, bytes, std::move(lg.work)};
       bytes = align(bytes + g.work.size() * sizeof(int2));
       d.groups.push_back(std::move(g));
     }
@@ -2134,7 +2234,10 @@ static mppi_status launch_batch_dynamic(const std::vector<BatchReq>& reqs, unsig
     int k = 0;
     for (auto& kv : pred_groups) {
       Dims dm;
-      for (int i : kv.second) dm.add(reqs[i].ctx);
+      for (int i : kv.second) {
+        dm.add(reqs[i].ctx);
+        dm.block_lds = std::max(dm.block_lds, path_block_bytes(reqs[i].ctx->m->host, reqs[i].ctx->E));
+      }
       HIP_TRY(launch_predict_batch(kv.first, (int)kv.second.size(), reinterpret_cast<const PredItem*>(dv + pred_off) + k,
                                    dm, s));
       k += (int)kv.second.size();

@@ -17,6 +17,9 @@ constexpr int kCt = 8;           // floats per contact row of that table
 constexpr int kMaxPaths = 8;     // path kernels: root-to-leaf paths (quads of lanes) per rollout
 constexpr int kMaxPath = 6;      // path kernels: bodies of a path
 constexpr int kPathRow = 28;     // floats per path, body and coordinate lane of their constants
+constexpr int kLaneRow = 52;     // floats per path and body of the constants of their one-lane form
+constexpr int kLaneExch = 28;    // floats per lane of its exchange records
+constexpr int kLaneItem = 1 << 30;  // in a work item's first sample: the one-lane form runs it
 constexpr int kPathExch = 20;    // floats per lane of their exchange records (14 used; staggers the banks)
 
 // Body row of the chain schedule's table (floats; integer fields stored as bits):
@@ -105,6 +108,9 @@ struct DevModel {
   // identity rotation, no mass, armature 1, so the body passes its parent's
   // frame on and hands nothing back.
   alignas(16) float path_rows[kMaxPaths][kMaxPath][3][kPathRow];
+  // the same constants for the form with one lane per path: P0 | P1 | P2 (27 and
+  // one unused), p_tree, axis_p, kp, kd, tau_max, [40] com, Ic, mass, armature
+  alignas(16) float lane_rows[kMaxPaths][kMaxPath][kLaneRow];
 };
 
 // Task targets of an instance's costs (Sec. IV-A), in a block of their own that
@@ -286,11 +292,17 @@ __host__ __device__ inline int chain_group_floats(int GC, int nb, int E, int nch
 
 // Path kernels: after the model table the constants of np paths of up to L
 // bodies (kPathRow floats per coordinate lane) and the exchange records of the
-// 64 lanes and one of zeros; per rollout group the knots and the costs by body.
+// 64 lanes and one of zeros; per rollout group the knots (at the end of a
+// rollout the costs by body, of which there are fewer, take their place).
 __host__ __device__ inline int path_table_floats(int nc, int np, int L) {
   return body_table_floats(nc) + np * L * 3 * kPathRow + 65 * kPathExch;
 }
-__host__ __device__ inline int path_group_floats(int nb, int E) { return ((E + 3) & ~3) + ((nb + 3) & ~3); }
+__host__ __device__ inline int path_group_floats(int E) { return (E + 3) & ~3; }
+
+// Their one-lane form: the same with kLaneRow floats per path and body.
+__host__ __device__ inline int lane_table_floats(int nc, int np, int L) {
+  return body_table_floats(nc) + np * L * kLaneRow + (L > 3 ? 65 * kLaneExch : 0);
+}
 
 // Team schedule: after the model table (then the team constants [slots][60] and
 // the slot of chain c's body at depth d [kMaxChains][kMaxLevels] as integer

@@ -26,6 +26,7 @@
 // which lane evaluates it), symmetric blocks hold U_min W_max in both
 // triangles, and sums over children and costs keep their order.
 #pragma once
+#include "mppi_step.hpp"
 
 namespace mppi {
 
@@ -515,8 +516,7 @@ __device__ __attribute__((always_inline)) void path_item(const DevInst& I, int f
   if (lane < kPathExch) exch[64 * kPathExch + lane] = 0.f;
   const int n = first + grp;
   const bool valid = n < I.N;
-  float* knots = smem + path_table_floats(nc, np, L) + grp * path_group_floats(nb, I.E);
-  float* red = knots + ((I.E + 3) & ~3);
+  float* knots = smem + path_table_floats(nc, np, L) + grp * path_group_floats(I.E);
   if (I.generate) {
     sample_group<G>(M, I, valid ? n : 0, l, knots, valid, tab, nominal_in);
   } else {
@@ -854,14 +854,15 @@ __device__ __attribute__((always_inline)) void path_item(const DevInst& I, int f
     }
     acc_base += I.w_H * e;
   }
+  wave_sync();  // the knots are not read any more: the costs by body take their place
 #pragma unroll
   for (int s = 0; s < S; ++s)
-    if (owner[s]) red[body[s]] = acc[s];
-  if (FB && l == 0) red[0] = acc_base;
+    if (owner[s]) knots[body[s]] = acc[s];
+  if (FB && l == 0) knots[0] = acc_base;
   wave_sync();
   if (l == 0 && valid) {
     float sum = 0.f;
-    for (int b = 0; b < nb; ++b) sum += red[b];
+    for (int b = 0; b < nb; ++b) sum += knots[b];
     if (!isfinite(sum)) sum = INFINITY;
     I.costs[n] = sum;
   }
@@ -870,45 +871,22 @@ __device__ __attribute__((always_inline)) void path_item(const DevInst& I, int f
 
 // The item function of an instance's tree (path_key in mppi_api.hip offers the
 // kernels only trees that one of these holds).
-template <bool FB>
+template <int L, bool FB>
 __device__ __forceinline__ void path_item_of(const DevInst& I, int first, float* smem, int steps, float* state_out,
                                              const float* x0_in, const float* nominal_in) {
   const int lanes = I.model->path_lanes;
-  if (I.model->path_len <= 3) {
-    if (lanes == 4) path_item<4, 3, FB>(I, first, smem, steps, state_out, x0_in, nominal_in);
-    else if (lanes == 8) path_item<8, 3, FB>(I, first, smem, steps, state_out, x0_in, nominal_in);
-    else if (lanes == 16) path_item<16, 3, FB>(I, first, smem, steps, state_out, x0_in, nominal_in);
-    else path_item<32, 3, FB>(I, first, smem, steps, state_out, x0_in, nominal_in);
-  } else {
-    if (lanes == 4) path_item<4, kMaxPath, FB>(I, first, smem, steps, state_out, x0_in, nominal_in);
-    else if (lanes == 8) path_item<8, kMaxPath, FB>(I, first, smem, steps, state_out, x0_in, nominal_in);
-    else if (lanes == 16) path_item<16, kMaxPath, FB>(I, first, smem, steps, state_out, x0_in, nominal_in);
-    else path_item<32, kMaxPath, FB>(I, first, smem, steps, state_out, x0_in, nominal_in);
-  }
+  if (lanes == 4) path_item<4, L, FB>(I, first, smem, steps, state_out, x0_in, nominal_in);
+  else if (lanes == 8) path_item<8, L, FB>(I, first, smem, steps, state_out, x0_in, nominal_in);
+  else if (lanes == 16) path_item<16, L, FB>(I, first, smem, steps, state_out, x0_in, nominal_in);
+  else path_item<32, L, FB>(I, first, smem, steps, state_out, x0_in, nominal_in);
 }
-
-// Block = one wavefront; work[blockIdx] = (instance, first sample) or, when work
-// is null, instance 0 and sample blockIdx * 64 / path_lanes (as rollout_kernel).
-// One launch takes trees of every kind, so the rollouts of a mixed batch run
-// side by side; the LDS layout is each instance's own.
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1, 1))) void path_kernel(
-    const DevInst* __restrict__ insts, const int2* __restrict__ work, const float* __restrict__ x0_in,
-    const float* __restrict__ nominal_in) {
-  extern __shared__ float smem[];
-  const int2 w = work ? work[blockIdx.x] : make_int2(0, (int)blockIdx.x * (64 / insts[0].model->path_lanes));
-  const DevInst& I = insts[w.x];
-  if (I.model->fb) path_item_of<true>(I, w.y, smem, I.H, nullptr, x0_in, nominal_in);
-  else path_item_of<false>(I, w.y, smem, I.H, nullptr, x0_in, nominal_in);
-}
-
-// State prediction (one workgroup per item: as predict_kernel); one: the item
-// itself where there is no table.
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1, 1))) void path_predict_kernel(
-    const PredItem* __restrict__ items, PredItem one) {
-  extern __shared__ float smem[];
-  const PredItem it = items ? items[blockIdx.x] : one;
-  if (it.inst->model->fb) path_item_of<true>(*it.inst, 0, smem, it.steps, it.state_out, nullptr, nullptr);
-  else path_item_of<false>(*it.inst, 0, smem, it.steps, it.state_out, nullptr, nullptr);
+template <bool FB>
+__device__ __forceinline__ void path_item_of(const DevInst& I, int first, float* smem, int steps, float* state_out,
+                                             const float* x0_in, const float* nominal_in) {
+  const int len = I.model->path_len;
+  if (len <= 3) path_item_of<3, FB>(I, first, smem, steps, state_out, x0_in, nominal_in);
+  else if (len <= 4) path_item_of<4, FB>(I, first, smem, steps, state_out, x0_in, nominal_in);
+  else path_item_of<kMaxPath, FB>(I, first, smem, steps, state_out, x0_in, nominal_in);
 }
 
 #undef Q0

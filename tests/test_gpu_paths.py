@@ -1,7 +1,7 @@
-"""The path kernels (one quad of lanes per root-to-leaf path of the tree) against
-the body schedule's kernel, bit for bit: the body schedule at its default lane
-count takes them, at any other lane count it does not, and a step's results do
-not depend on the lane count.  Trees of every kind the kernels are compiled for
+"""The path kernel (a quad of lanes, or one lane, per root-to-leaf path of the
+tree) against the body schedule's kernel, bit for bit: the body schedule at its default lane
+count takes it, at any other lane count it does not, and a step's results do
+not depend on the lane count.  Trees of every kind the kernel is compiled for
 (path counts, path lengths, fixed and floating bases, bodies that several paths
 share, contacts on inner bodies and on the base), at the sample counts where a
 wavefront is partly filled."""
@@ -133,6 +133,34 @@ def test_path_kernel_equals_body_schedule(name, n):
     _same(a, b, (name, n))
 
 
+def _past_one_turn(m):
+    """Just more samples than the quad form's wavefronts of one turn of the device
+    (four SIMDs per compute unit) hold: the one-lane form's range begins."""
+    leaves = len(set(range(len(m["parent"]))) - set(int(p) for p in m["parent"]) - ({0} if m["floating_base"] else set()))
+    lanes = 4 * (1 if leaves <= 1 else 2 if leaves <= 2 else 4 if leaves <= 4 else 8)
+    return 4 * torch.cuda.get_device_properties(0).multi_processor_count * (64 // lanes) + 37
+
+
+@pytest.mark.parametrize("name", sorted(TREES))
+def test_one_lane_form_equals_body_schedule(name):
+    m = TREES[name]()
+    n = _past_one_turn(m)
+    a, b = _both(m, _params(m, n, horizon=7, iters=1))
+    print(f"{name} N={n}: costs[0][:3] {a['costs'][0][:3]}")
+    assert np.any(np.isfinite(a["costs"]))
+    _same(a, b, (name, n))
+
+
+@pytest.mark.parametrize("more", [dict(spline_mode=1), dict(spline_mode=2, knots=4), dict(substeps=3),
+                                  dict(weight_mode=1, horizon=1), dict(q_des=[0.96, 0.0, 0.28, 0.0]), dict(knots=40)])
+def test_one_lane_form_options(more):
+    more = dict(more)
+    m = dict(TREES["quadruped"]())
+    m["n_substeps"] = more.pop("substeps", 1)
+    a, b = _both(m, _params(m, _past_one_turn(m), **{"horizon": 7, "iters": 1, **more}))
+    _same(a, b, more)
+
+
 @pytest.mark.parametrize("name", ["arm", "quadruped", "humanoid", "forked_legs"])
 @pytest.mark.parametrize("more", [dict(spline_mode=1), dict(spline_mode=2, knots=4), dict(substeps=3),
                                   dict(weight_mode=1, horizon=1), dict(q_des=[0.96, 0.0, 0.28, 0.0])])
@@ -178,10 +206,13 @@ def test_prediction_equals_the_traced_rollout(name):
         assert np.array_equal(out.cpu().numpy(), trace[0, n, :nx].cpu().numpy()), (name, n)
 
 
-def test_mixed_batch_equals_plain_steps():
+@pytest.mark.parametrize("scale", [1, 40])
+def test_mixed_batch_equals_plain_steps(scale):
+    """scale 1: the batch fits the device at once (quad form); 40: it does not (both
+    forms in one launch)."""
     names = ["arm", "quadruped", "humanoid", "ytree", "hexapod", "quadruped"]
     ms = [TREES[n]() for n in names]
-    ps = [_params(m, 11 + 6 * i, horizon=15 + i, iters=1 + i % 3) for i, m in enumerate(ms)]
+    ps = [_params(m, 11 * scale + 6 * i, horizon=15 + i * i, iters=1 + i % 3) for i, m in enumerate(ms)]
     models = [mppi.Model(m) for m in ms]
     plain = [_step(mppi.Controller(md, p, 9 + i), m, p) for i, (md, m, p) in enumerate(zip(models, ms, ps))]
     ctrls = [mppi.Controller(md, p, 9 + i) for i, (md, p) in enumerate(zip(models, ps))]
