@@ -15,7 +15,7 @@
 // with the other levels' lanes idle; here the sweeps keep three lanes in four
 // busy and need no lane masks and no exchange between levels.  Issue slots
 // (quarter-rate cycles) per step and wavefront, body schedule -> here: quadruped
-// 2 213 -> 1 860, humanoid 5 085 -> 3 950, arm 1 650 -> 960; a launch at 256
+// 2 213 -> 1 820, humanoid 5 085 -> 3 900, arm 1 650 -> 960; a launch at 256
 // samples x 200 steps of the quadruped takes 0.78 -> 0.61 ms (4 096 samples: 0.74
 // -> 0.64), at 256 x 150 of the humanoid 1.33 -> 1.01 ms, at 32 x 50 of the arm
 // 0.140 -> 0.092 ms.  The form needs more than 256 registers, so a SIMD holds
@@ -248,13 +248,23 @@ __device__ __forceinline__ float path_contact(const float* r, const PathFrame& F
                                               const ContactLaw& law, int k, const float* sgn, PathInertia& I, float* vw,
                                               float* fw) {
   const float* Rb = B.Rb;
-  const float x = F.R[0] * r[0] + F.R[1] * r[1] + F.R[2] * r[2];
-  const float x1 = rot1(x), x2_ = rot2(x);
-  const float wx = cross_k(rot1(F.va), rot2(F.va), x1, x2_);
-  const Rep3 vB = rep3(F.vl + wx), xB = rep3(F.p + x);
-  const float pw2 = B.pz + Rb[6] * xB.x0 + Rb[7] * xB.x1 + Rb[8] * xB.x2;
-#pragma unroll
-  for (int q = 0; q < 3; ++q) vw[q] = Rb[q * 3 + 0] * vB.x0 + Rb[q * 3 + 1] * vB.x1 + Rb[q * 3 + 2] * vB.x2;
+  // the point x (about the body's origin), its height pw2 and world velocity vw
+  float x, x1, x2_, pw2, vB, xB;
+  asm("v_mul_f32 %0, %10, %13\n"
+      "v_fmac_f32 %0, %9, %12\n"
+      "v_fmac_f32 %0, %11, %14\n"
+      "v_mov_b32 %3, %18\n"
+      "v_add_f32 %8, %17, %0\n"
+      MOV "%1, %0" ROT1 MOV "%2, %0" ROT2
+      MUL "%7, -%15, %1" ROT2 FMAC "%7, %15, %2" ROT1
+      "v_add_f32 %7, %16, %7\n"
+      FMAC "%3, %8, %25" Q0 FMAC "%3, %8, %26" Q1 FMAC "%3, %8, %27" Q2
+      MUL "%4, %7, %20" Q1 MUL "%5, %7, %23" Q1 MUL "%6, %7, %26" Q1
+      FMAC "%4, %7, %19" Q0 FMAC "%5, %7, %22" Q0 FMAC "%6, %7, %25" Q0
+      FMAC "%4, %7, %21" Q2 FMAC "%5, %7, %24" Q2 FMAC "%6, %7, %27" Q2
+      : "=&v"(x), "=&v"(x1), "=&v"(x2_), "=&v"(pw2), "=&v"(vw[0]), "=&v"(vw[1]), "=&v"(vw[2]), "=&v"(vB), "=&v"(xB)
+      : "v"(F.R[0]), "v"(F.R[1]), "v"(F.R[2]), "v"(r[0]), "v"(r[1]), "v"(r[2]), "v"(F.va), "v"(F.vl), "v"(F.p), "v"(B.pz),
+        "v"(Rb[0]), "v"(Rb[1]), "v"(Rb[2]), "v"(Rb[3]), "v"(Rb[4]), "v"(Rb[5]), "v"(Rb[6]), "v"(Rb[7]), "v"(Rb[8]));
   float fn = 0.f;
   if (pw2 < 0.f) fn = fmaxf(0.f, -law.k * pw2 - law.d * vw[2]);
   const float n2 = vw[0] * vw[0] + vw[1] * vw[1] + law.eps * law.eps;
@@ -262,53 +272,106 @@ __device__ __forceinline__ float path_contact(const float* r, const PathFrame& F
   const float mfn = law.mu * fn * inv_nrm;
   fw[0] = -mfn * vw[0]; fw[1] = -mfn * vw[1]; fw[2] = fn;
   if (fn > 0.f) {  // (without force the terms below are all zero)
-    const float fB = B.c0 * fw[0] + B.c1 * fw[1] + B.c2 * fw[2];
-    const float xf = cross_k(x1, x2_, rot1(fB), rot2(fB));
-    I.pa -= xf;
-    I.pl -= fB;
     const float aa = mfn;
     const float al = law.d - aa;
     const float zb = B.c2;
     const float wt[2] = {vw[0] * inv_nrm, vw[1] * inv_nrm};
-    const float ub = B.c0 * wt[0] + B.c1 * wt[1];
-    const float w1 = cross_k(x1, x2_, rot1(zb), rot2(zb));
-    const float w2 = cross_k(x1, x2_, rot1(ub), rot2(ub));
-    const Rep3 xr = rep3(x), ur = rep3(ub);
+    // fB = Rb^T fw, ub = Rb^T wt, w1 = x x zb, w2 = x x ub; the force on the body
+    float fB, ub, w1, w2, xf;
+    asm("v_mul_f32 %0, %10, %13\n"
+        "v_mul_f32 %1, %10, %16\n"
+        "v_fmac_f32 %1, %9, %15\n"
+        "v_fmac_f32 %0, %9, %12\n"
+        "v_fmac_f32 %0, %11, %14\n"
+        MUL "%2, -%11, %8" ROT1 FMAC "%2, %11, %7" ROT2
+        MUL "%3, -%1, %8" ROT1 FMAC "%3, %1, %7" ROT2
+        MUL "%4, -%0, %8" ROT1 FMAC "%4, %0, %7" ROT2
+        "v_sub_f32 %6, %6, %0\n"
+        "v_sub_f32 %5, %5, %4\n"
+        : "=&v"(fB), "=&v"(ub), "=&v"(w1), "=&v"(w2), "=&v"(xf), "+v"(I.pa), "+v"(I.pl)
+        : "v"(x1), "v"(x2_), "v"(B.c0), "v"(B.c1), "v"(zb), "v"(fw[0]), "v"(fw[1]), "v"(fw[2]), "v"(wt[0]), "v"(wt[1]));
+    const Rep3 xr = rep3(x);
     const float x2 = xr.x0 * xr.x0 + xr.x1 * xr.x1 + xr.x2 * xr.x2;
     const float dta = dt * aa, dtal = dt * al;
     // y1 = (w1, zb), y2 = (w2, ub); t1 = dtal y1, t2 = dta y2
     const float t1a = dtal * w1, t1l = dtal * zb, t2a = dta * w2, t2l = dta * ub;
-    I.A[0] += quad0(t1a) * w1 - quad0(t2a) * w2;
-    I.A[1] += lo1(t1a) * hi1(w1) - lo1(t2a) * hi1(w2);
-    I.A[2] += t1a * quad2(w1) - t2a * quad2(w2);
-    const float zj[3] = {Rb[6], Rb[7], Rb[8]}, uj[3] = {ur.x0, ur.x1, ur.x2};
-    const Rep3 p1 = rep3(t1a), p2 = rep3(t2a);
-    const float p1j[3] = {p1.x0, p1.x1, p1.x2}, p2j[3] = {p2.x0, p2.x1, p2.x2};
-#pragma unroll
-    for (int j = 0; j < 3; ++j) {
-      I.B[j] += t1a * zj[j] - t2a * uj[j];
-      I.T[j] += p1j[j] * zb - p2j[j] * ub;
-    }
-    I.C[0] += quad0(t1l) * zb - quad0(t2l) * ub;
-    I.C[1] += lo1(t1l) * hi1(zb) - lo1(t2l) * hi1(ub);
-    I.C[2] += t1l * zj[2] - t2l * uj[2];
     const float dax = dta * x;
     const float dx2 = dta * x2;
-    I.A[0] += (k == 0 ? dx2 : 0.f) - quad0(dax) * x;
-    I.A[1] += (k == 1 ? dx2 : 0.f) - lo1(dax) * hi1(x);
-    I.A[2] += (k == 2 ? dx2 : 0.f) - dax * xr.x2;
-    const float d0 = sgn[0] * skew_part<0>(dax), d1 = sgn[1] * skew_part<1>(dax), d2 = sgn[2] * skew_part<2>(dax);
-    I.B[0] += d0; I.B[1] += d1; I.B[2] += d2;
-    I.T[0] -= d0; I.T[1] -= d1; I.T[2] -= d2;
-#pragma unroll
-    for (int j = 0; j < 3; ++j) I.C[j] += k == j ? dta : 0.f;
-    const float sa = -F.ba;
+    float s0 = k == 0 ? dx2 : 0.f, s1 = k == 1 ? dx2 : 0.f, s2 = k == 2 ? dx2 : 0.f;
+    const float dk0 = k == 0 ? dta : 0.f, dk1 = k == 1 ? dta : 0.f, dk2 = k == 2 ? dta : 0.f;
+    float a, b, h1, h2;
+    // A_rc += t1_r y1_c - t2_r y2_c (r <= c), then += (r == c ? dx2 : 0) - dax_r x_c; C alike with dta on the diagonal
+    asm("s_nop 1\n"
+        MUL "%9, -%14, %18" Q0 MUL "%10, -%18, %14" Q2
+        FMAC "%9, %13, %17" Q0 FMAC "%10, %17, %13" Q2
+        MOV "%11, %17" HI1 MOV "%12, %18" HI1
+        "v_add_f32 %0, %0, %9\n"
+        "v_add_f32 %2, %2, %10\n"
+        MUL "%9, -%14, %12" LO1 FMAC "%9, %13, %11" LO1
+        MOV "%11, %22" HI1
+        FMAC "%6, -%21, %22" Q0 FMAC "%8, -%22, %21" Q2 FMAC "%7, -%21, %11" LO1
+        "v_add_f32 %1, %1, %9\n"
+        "v_add_f32 %0, %0, %6\n"
+        "v_add_f32 %2, %2, %8\n"
+        "v_add_f32 %1, %1, %7\n"
+        MUL "%9, -%16, %20" Q0 MUL "%10, -%20, %16" Q2
+        FMAC "%9, %15, %19" Q0 FMAC "%10, %19, %15" Q2
+        MOV "%11, %19" HI1 MOV "%12, %20" HI1
+        "v_add_f32 %3, %3, %9\n"
+        "v_add_f32 %5, %5, %10\n"
+        MUL "%9, -%16, %12" LO1 FMAC "%9, %15, %11" LO1
+        "v_add_f32 %3, %3, %23\n"
+        "v_add_f32 %5, %5, %25\n"
+        "v_add_f32 %4, %4, %9\n"
+        "v_add_f32 %4, %4, %24\n"
+        : "+v"(I.A[0]), "+v"(I.A[1]), "+v"(I.A[2]), "+v"(I.C[0]), "+v"(I.C[1]), "+v"(I.C[2]), "+v"(s0), "+v"(s1),
+          "+v"(s2), "=&v"(a), "=&v"(b), "=&v"(h1), "=&v"(h2)
+        : "v"(t1a), "v"(t2a), "v"(t1l), "v"(t2l), "v"(w1), "v"(w2), "v"(zb), "v"(ub), "v"(dax), "v"(x), "v"(dk0),
+          "v"(dk1), "v"(dk2));
+    // B_j += t1a zb_j - t2a ub_j, T_j += t1a_j zb - t2a_j ub, then the skew part of dax
+    asm("s_nop 1\n"
+        MUL "%6, -%11, %9" Q0 MUL "%7, -%11, %9" Q1
+        "v_fmac_f32 %6, %16, %8\n"
+        "v_fmac_f32 %7, %17, %8\n"
+        "v_add_f32 %0, %0, %6\n"
+        "v_add_f32 %1, %1, %7\n"
+        MUL "%6, -%11, %9" Q2 MUL "%7, -%9, %11" Q0
+        "v_fmac_f32 %6, %18, %8\n"
+        FMAC "%7, %8, %10" Q0
+        "v_add_f32 %2, %2, %6\n"
+        "v_add_f32 %3, %3, %7\n"
+        MUL "%6, -%9, %11" Q1 MUL "%7, -%9, %11" Q2
+        FMAC "%6, %8, %10" Q1 FMAC "%7, %8, %10" Q2
+        "v_add_f32 %4, %4, %6\n"
+        "v_add_f32 %5, %5, %7\n"
+        MUL "%6, %12, %13 quad_perm:[0,2,1,1]\n"
+        MUL "%7, %12, %14 quad_perm:[2,1,0,0]\n"
+        "v_add_f32 %0, %0, %6\n"
+        "v_sub_f32 %3, %3, %6\n"
+        MUL "%6, %12, %15 quad_perm:[1,0,2,2]\n"
+        "v_add_f32 %1, %1, %7\n"
+        "v_sub_f32 %4, %4, %7\n"
+        "v_add_f32 %2, %2, %6\n"
+        "v_sub_f32 %5, %5, %6\n"
+        : "+v"(I.B[0]), "+v"(I.B[1]), "+v"(I.B[2]), "+v"(I.T[0]), "+v"(I.T[1]), "+v"(I.T[2]), "=&v"(a), "=&v"(b)
+        : "v"(t1a), "v"(t2a), "v"(zb), "v"(ub), "v"(dax), "v"(sgn[0]), "v"(sgn[1]), "v"(sgn[2]), "v"(Rb[6]), "v"(Rb[7]),
+          "v"(Rb[8]));
+    // w3 = (agl - beta) + (-beta_a) x x, zw = zb . w3, uw = ub . w3
     const float sl = B.agl - F.bl;
-    const float sx = cross_k(rot1(sa), rot2(sa), x1, x2_);
-    const float w3 = sl + sx;
-    const Rep3 w = rep3(w3);
-    const float zw = zj[0] * w.x0 + zj[1] * w.x1 + zj[2] * w.x2;
-    const float uw = uj[0] * w.x0 + uj[1] * w.x1 + uj[2] * w.x2;
+    float w3, zw, uw, g0, g1, g2;
+    asm("s_nop 1\n"
+        MUL "%0, %6, %8" ROT2 FMAC "%0, -%6, %9" ROT1
+        "v_add_f32 %0, %7, %0\n"
+        "s_nop 1\n"
+        MOV "%3, %0" Q0 MOV "%4, %0" Q1 MOV "%5, %0" Q2
+        "v_mul_f32 %1, %12, %4\n"
+        MUL "%2, %10, %4" Q1
+        "v_fmac_f32 %1, %11, %3\n"
+        FMAC "%2, %10, %3" Q0
+        "v_fmac_f32 %1, %13, %5\n"
+        FMAC "%2, %10, %5" Q2
+        : "=&v"(w3), "=&v"(zw), "=&v"(uw), "=&v"(g0), "=&v"(g1), "=&v"(g2)
+        : "v"(F.ba), "v"(sl), "v"(x1), "v"(x2_), "v"(ub), "v"(Rb[6]), "v"(Rb[7]), "v"(Rb[8]));
     const float Dw3 = aa * w3 + al * zw * zb - aa * uw * ub;
     const float xd = cross_k(x1, x2_, rot1(Dw3), rot2(Dw3));
     I.pa += dt * xd;
@@ -438,6 +501,80 @@ __device__ __forceinline__ float path_forward(float ala, float all, const PathFr
   return qdd;
 }
 
+// base_solve over the rows of a row of 16 lanes, whose first quad holds the sums:
+// lanes 0..2 take rows 0..2 of the 6x6 inertia, lanes 4..6 rows 3..5 (the first
+// quad's columns of B and rows of C), and a column of the factor is one value
+// per lane; a0 comes out on every lane.
+#define BC0 " row_newbcast:0\n"
+#define BC1 " row_newbcast:1\n"
+#define BC2 " row_newbcast:2\n"
+#define BC3 " row_newbcast:4\n"
+#define BC4 " row_newbcast:5\n"
+#define BC5 " row_newbcast:6\n"
+__device__ __forceinline__ float second_quad(float first, float second) {
+  // lanes 4..7 take the second value of the first quad, the others keep the first
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(__builtin_bit_cast(int, first),
+                                                               __builtin_bit_cast(int, second), 0x114, 0xf, 0x2, false));
+}
+__device__ __forceinline__ void path_base_solve(const PathInertia& I, float* a) {
+  float m[6], v[6], y[6];
+#pragma unroll
+  for (int j = 0; j < 3; ++j) {
+    m[j] = second_quad(I.A[j], I.T[j]);
+    m[3 + j] = second_quad(I.B[j], I.C[j]);
+  }
+  float s = -second_quad(I.pa, I.pl);
+  // Factor: v_j = 1 / sqrt(m_j's diagonal) on its own lane, column m_j times it,
+  // then subtracted from the later columns (each takes them in order); forward
+  // substitution beside it: y_j = s v_j on its own lane, s -= y_j m_j.  Back
+  // substitution on every lane: a_i = (y_i - sum over k > i of m_i's row k times a_k) v_i.
+  // The independent instructions stand where a value just written has to wait
+  // before it is read through DPP.
+#define RSQ "v_rsq_f32 "
+#define VMUL "v_mul_f32 "
+  asm("s_nop 1\n"
+      RSQ "%7, %0\ns_nop 1\n" MUL "%0, %7, %0" BC0
+      VMUL "%13, %6, %7\ns_nop 0\n"
+      FMAC "%1, -%0, %0" BC1
+      RSQ "%8, %1\n" FMAC "%2, -%0, %0" BC2 FMAC "%3, -%0, %0" BC3 MUL "%1, %8, %1" BC1
+      FMAC "%4, -%0, %0" BC4 FMAC "%5, -%0, %0" BC5
+      FMAC "%2, -%1, %1" BC2
+      RSQ "%9, %2\n" FMAC "%3, -%1, %1" BC3 FMAC "%4, -%1, %1" BC4 MUL "%2, %9, %2" BC2
+      FMAC "%5, -%1, %1" BC5 FMAC "%6, -%13, %0" BC0
+      FMAC "%3, -%2, %2" BC3
+      RSQ "%10, %3\n" FMAC "%4, -%2, %2" BC4 FMAC "%5, -%2, %2" BC5 MUL "%3, %10, %3" BC3
+      VMUL "%14, %6, %8\ns_nop 0\n"
+      FMAC "%4, -%3, %3" BC4
+      RSQ "%11, %4\n" FMAC "%5, -%3, %3" BC5 FMAC "%6, -%14, %1" BC1 MUL "%4, %11, %4" BC4
+      VMUL "%15, %6, %9\ns_nop 0\n"
+      FMAC "%5, -%4, %4" BC5
+      RSQ "%12, %5\n" FMAC "%6, -%15, %2" BC2
+      VMUL "%16, %6, %10\ns_nop 1\n" FMAC "%6, -%16, %3" BC3
+      VMUL "%17, %6, %11\ns_nop 1\n" FMAC "%6, -%17, %4" BC4
+      VMUL "%18, %6, %12\n"
+      MOV "%23, %17" BC4 MOV "%22, %16" BC3 MOV "%21, %15" BC2 MOV "%20, %14" BC1 MOV "%19, %13" BC0
+      MOV "%24, %18" BC5
+      MUL "%24, %12, %24" BC5
+      FMAC "%23, -%4, %24" BC5 MUL "%23, %11, %23" BC4
+      FMAC "%22, -%3, %23" BC4 FMAC "%22, -%3, %24" BC5 MUL "%22, %10, %22" BC3
+      FMAC "%21, -%2, %22" BC3 FMAC "%21, -%2, %23" BC4 FMAC "%21, -%2, %24" BC5 MUL "%21, %9, %21" BC2
+      FMAC "%20, -%1, %21" BC2 FMAC "%20, -%1, %22" BC3 FMAC "%20, -%1, %23" BC4 FMAC "%20, -%1, %24" BC5
+      MUL "%20, %8, %20" BC1
+      FMAC "%19, -%0, %20" BC1 FMAC "%19, -%0, %21" BC2 FMAC "%19, -%0, %22" BC3 FMAC "%19, -%0, %23" BC4
+      FMAC "%19, -%0, %24" BC5 MUL "%19, %7, %19" BC0
+      : "+v"(m[0]), "+v"(m[1]), "+v"(m[2]), "+v"(m[3]), "+v"(m[4]), "+v"(m[5]), "+v"(s), "=&v"(v[0]), "=&v"(v[1]),
+        "=&v"(v[2]), "=&v"(v[3]), "=&v"(v[4]), "=&v"(v[5]), "=&v"(y[0]), "=&v"(y[1]), "=&v"(y[2]), "=&v"(y[3]),
+        "=&v"(y[4]), "=&v"(y[5]), "=&v"(a[0]), "=&v"(a[1]), "=&v"(a[2]), "=&v"(a[3]), "=&v"(a[4]), "=&v"(a[5]));
+#undef RSQ
+#undef VMUL
+}
+#undef BC0
+#undef BC1
+#undef BC2
+#undef BC3
+#undef BC4
+#undef BC5
+
 // A lane's record of the exchange area (children reached through LDS).
 __device__ __forceinline__ void put_exchange(float* d, const PathInertia& x) {
   put4(d, x.A[0], x.A[1], x.A[2], x.pa);
@@ -483,14 +620,19 @@ __device__ __forceinline__ float from_first_quad(float x) {
 // One work item: 64 / G rollouts of one instance, samples first .. first + 64/G - 1
 // (those >= N are computed but not stored).  L: the longest path the kernel
 // holds; FB: floating base.  Paths that share a body, or more than four of them
-// on a base, meet through LDS.  The L = 3 kernel keeps a body's constants in
-// registers; the L = 6 kernel reads them from LDS at each use (they would not fit).
+// on a base, meet through LDS.  A body's constants stay in registers where the
+// 256 the vector instructions address hold them (a fixed-base arm of three
+// bodies); beside a floating base's state the inertias are read from LDS at each
+// use (in registers they would be fetched back from the accumulation file: 59
+// moves a step, 0.653 -> 0.644 ms at 256 x 200 steps of the quadruped), and so are
+// all constants of longer paths.
 template <int G, int L, bool FB>
 __device__ __attribute__((always_inline)) void path_item(const DevInst& I, int first, float* smem, int steps,
                                                          float* state_out, const float* x0_in,
                                                          const float* nominal_in) {
   constexpr int S = (L + 2) / 3;      // joints a lane looks after (joint 3 s + k of its path)
-  constexpr bool kRegs = L <= 3;
+  constexpr bool kRegs = L <= 3;           // (see above)
+  constexpr bool kMassRegs = kRegs && !FB;
   constexpr bool kBranch = L > 3;     // paths may share bodies
   const float* x0 = x0_in ? x0_in : I.x0;
   switch (I.wave_prio) {
@@ -532,12 +674,12 @@ __device__ __attribute__((always_inline)) void path_item(const DevInst& I, int f
   const int pp = path < np ? path : np - 1;
   const float* my_rows = rows + path_row(pp, L, 0, k);
   PathFk KF[kRegs ? L : 1];
-  PathMass KM[kRegs ? L : 1];
+  PathMass KM[kMassRegs ? L : 1];
   if constexpr (kRegs) {
 #pragma unroll
     for (int i = 0; i < L; ++i) {
       KF[i] = load_path_fk(my_rows + i * 3 * kPathRow);
-      KM[i] = load_path_mass(my_rows + i * 3 * kPathRow);
+      if constexpr (kMassRegs) KM[i] = load_path_mass(my_rows + i * 3 * kPathRow);
     }
   }
   int ct_of[L];            // contacts of body i: first row | count << 8
@@ -689,7 +831,7 @@ __device__ __attribute__((always_inline)) void path_item(const DevInst& I, int f
 #pragma unroll
     for (int i = L - 1; i >= 0; --i) {
       const int s = i / 3;
-      const PathMass K = kRegs ? KM[kRegs ? i : 0] : load_path_mass(my_rows + i * 3 * kPathRow);
+      const PathMass K = kMassRegs ? KM[kMassRegs ? i : 0] : load_path_mass(my_rows + i * 3 * kPathRow);
       PathInertia IA;
       path_inertia(Fr[i].R, K, k, sgn, IA);
       path_bias(Fr[i].va, Fr[i].vl, K.m, IA);
@@ -758,22 +900,27 @@ __device__ __attribute__((always_inline)) void path_item(const DevInst& I, int f
         if (G > 8 && (base_mask & 4u)) add_row_lane<8>(IA, Ip);
         if (G > 8 && (base_mask & 8u)) add_row_lane<12>(IA, Ip);
       }
-      float X[21], px[6], a0[6];
+      float a0[6];
+      if constexpr (G >= 16) {
+        path_base_solve(IA, a0);
+      } else {
+        float X[21], px[6];
 #pragma unroll
-      for (int c = 0; c < 3; ++c) {
-        X[SI(0, c)] = from_first_quad<G, 0>(IA.A[c]);
-        if (c >= 1) X[SI(1, c)] = from_first_quad<G, 1>(IA.A[c]);
-        if (c >= 2) X[SI(2, c)] = from_first_quad<G, 2>(IA.A[c]);
-        X[SI(0, 3 + c)] = from_first_quad<G, 0>(IA.B[c]);
-        X[SI(1, 3 + c)] = from_first_quad<G, 1>(IA.B[c]);
-        X[SI(2, 3 + c)] = from_first_quad<G, 2>(IA.B[c]);
-        X[SI(3, 3 + c)] = from_first_quad<G, 0>(IA.C[c]);
-        if (c >= 1) X[SI(4, 3 + c)] = from_first_quad<G, 1>(IA.C[c]);
-        if (c >= 2) X[SI(5, 3 + c)] = from_first_quad<G, 2>(IA.C[c]);
+        for (int c = 0; c < 3; ++c) {
+          X[SI(0, c)] = from_first_quad<G, 0>(IA.A[c]);
+          if (c >= 1) X[SI(1, c)] = from_first_quad<G, 1>(IA.A[c]);
+          if (c >= 2) X[SI(2, c)] = from_first_quad<G, 2>(IA.A[c]);
+          X[SI(0, 3 + c)] = from_first_quad<G, 0>(IA.B[c]);
+          X[SI(1, 3 + c)] = from_first_quad<G, 1>(IA.B[c]);
+          X[SI(2, 3 + c)] = from_first_quad<G, 2>(IA.B[c]);
+          X[SI(3, 3 + c)] = from_first_quad<G, 0>(IA.C[c]);
+          if (c >= 1) X[SI(4, 3 + c)] = from_first_quad<G, 1>(IA.C[c]);
+          if (c >= 2) X[SI(5, 3 + c)] = from_first_quad<G, 2>(IA.C[c]);
+        }
+        px[0] = from_first_quad<G, 0>(IA.pa); px[1] = from_first_quad<G, 1>(IA.pa); px[2] = from_first_quad<G, 2>(IA.pa);
+        px[3] = from_first_quad<G, 0>(IA.pl); px[4] = from_first_quad<G, 1>(IA.pl); px[5] = from_first_quad<G, 2>(IA.pl);
+        base_solve(X, px, a0);
       }
-      px[0] = from_first_quad<G, 0>(IA.pa); px[1] = from_first_quad<G, 1>(IA.pa); px[2] = from_first_quad<G, 2>(IA.pa);
-      px[3] = from_first_quad<G, 0>(IA.pl); px[4] = from_first_quad<G, 1>(IA.pl); px[5] = from_first_quad<G, 2>(IA.pl);
-      base_solve(X, px, a0);
       const float g = sc.g;
       const float agl[3] = {-g * B.Rb[6], -g * B.Rb[7], -g * B.Rb[8]};
       ba[0] = a0[0]; ba[1] = a0[1]; ba[2] = a0[2];
