@@ -49,7 +49,7 @@ __global__ void shift_knots_kernel(const float*, float*, int, int, int, int, int
 template <int G>
 __global__ void dynamics_kernel(const DevModel*, int, const float*, const float*, const float*, const float*, float,
                                 float*, int, int);
-template <int T> __global__ void update_kernel(const DevUpdate*, const UpdateOut*, UpdateOut);
+template <int T, int NT> __global__ void update_kernel(const DevUpdate*, const UpdateOut*, UpdateOut);
 __global__ void update_single_kernel(DevUpdate);
 __global__ void set_targets_kernel(DevTargets*, DevTargets);
 struct StageItem {
@@ -1172,9 +1172,11 @@ static std::atomic<int> g_persistent{0};
 // parts, then n256 of at most parts256.
 struct UpdGrid {
   int n64 = 0, parts64 = 1, n256 = 0, parts256 = 1;
+  int all64 = 0;  // parts of the 64-thread updates together
   void add(const DevUpdate& u) {
     if (u.threads == 64) {
       ++n64;
+      all64 += u.parts;
       parts64 = std::max(parts64, u.parts);
     } else {
       ++n256;
@@ -1188,16 +1190,19 @@ static void order_by_update_shape(std::vector<int>& idx, const std::function<int
 }
 static hipError_t launch_updates(const DevUpdate* ups, const UpdateOut* outs, const UpdGrid& g, hipStream_t s) {
   const UpdateOut none{nullptr, nullptr, nullptr, nullptr};
-  if (g.n64 > 0) hipLaunchKernelGGL(update_kernel<64>, dim3(g.parts64, g.n64), dim3(64), 0, s, ups, outs, none);
+  if (g.n64 > 0 && g.all64 <= kUpdWideParts)
+    hipLaunchKernelGGL((update_kernel<64, 256>), dim3(g.parts64, g.n64), dim3(256), 0, s, ups, outs, none);
+  else if (g.n64 > 0)
+    hipLaunchKernelGGL((update_kernel<64, 64>), dim3(g.parts64, g.n64), dim3(64), 0, s, ups, outs, none);
   if (g.n256 > 0)
-    hipLaunchKernelGGL(update_kernel<kUpdThreads>, dim3(g.parts256, g.n256), dim3(kUpdThreads), 0, s, ups + g.n64,
+    hipLaunchKernelGGL((update_kernel<256, 256>), dim3(g.parts256, g.n256), dim3(256), 0, s, ups + g.n64,
                        outs ? outs + g.n64 : nullptr, none);
   return hipGetLastError();
 }
 // one instance's update (its shape), with the call's outputs o
 static hipError_t launch_update1(const DevUpdate* u, const DevUpdate& h, const UpdateOut& o, hipStream_t s) {
-  if (h.threads == 64) hipLaunchKernelGGL(update_kernel<64>, dim3(h.parts, 1), dim3(64), 0, s, u, nullptr, o);
-  else hipLaunchKernelGGL(update_kernel<kUpdThreads>, dim3(h.parts, 1), dim3(kUpdThreads), 0, s, u, nullptr, o);
+  if (h.threads == 64) hipLaunchKernelGGL((update_kernel<64, 256>), dim3(h.parts, 1), dim3(256), 0, s, u, nullptr, o);
+  else hipLaunchKernelGGL((update_kernel<256, 256>), dim3(h.parts, 1), dim3(256), 0, s, u, nullptr, o);
   return hipGetLastError();
 }
 

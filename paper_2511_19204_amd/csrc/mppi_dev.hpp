@@ -172,7 +172,7 @@ struct DevUpdate {
   float* partial;        // [update_parts(N)][E] per-part weighted sums (scratch)
   uint32_t* done;        // parts finished in the current launch (0 between launches)
   int32_t N, E, iter, weight_mode, first_iter, last_iter, parts;
-  int32_t threads;       // workgroup size of the instance's update launches (update_shape)
+  int32_t threads;       // width of the sums' order (update_shape)
   float lambda;
 };
 
@@ -213,13 +213,12 @@ __host__ __device__ inline int update_parts(int N) {
   const int p = (N + kUpdMinSlice - 1) / kUpdMinSlice;
   return p < 1 ? 1 : (p > kUpdMaxParts ? kUpdMaxParts : p);
 }
-// Workgroup size and parts of an instance's update.  Up to 1024 samples (the
-// sizes served together with other instances' rollouts) the workgroups are one
-// wavefront of 64 threads over slices of 16 samples: a wavefront needs the
-// registers of one SIMD where a rollout wavefront has ended, while a 256-thread
-// workgroup needs four of them on one compute unit, which a device full of
-// rollouts rarely has.  Larger instances take 256 threads over slices of 64.
-// The shape depends on N only, so an instance's sums are the same in every path.
+// Order and parts of an instance's update: the sums are those of `threads` threads
+// per part, up to 1024 samples 64 threads over slices of 16 samples, beyond that
+// 256 over slices of 64.  The shape depends on N only, so an instance's sums are
+// the same in every path.  The workgroups have as many threads, or at 64 four
+// times as many (the same sums) in launches of at most kUpdWideParts parts.
+constexpr int kUpdWideParts = 1024;
 struct UpdShape {
   int threads, parts;
 };

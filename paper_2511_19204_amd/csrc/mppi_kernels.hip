@@ -1391,28 +1391,43 @@ __global__ void reset_counters(unsigned int* __restrict__ c, int n) {
 // out (per call): the final nominal, best knots and info of the last iteration.
 // ---------------------------------------------------------------------------
 
-// The update's workgroups have T threads (64 or 256, update_shape).
+// T (64 or 256, update_shape) is the width of the sums' order: the weight sum and
+// a slice's knot sums are taken as T threads would take them.  A workgroup of NT =
+// T threads draws each element block's rows in the block's own thread.  At T = 64
+// a workgroup of NT = 256 shares what has no order -- the statistics, the weights
+// and, above all, the draws of a slice's samples, about 330 instructions each --
+// and so ends sooner: an update of the hexapod takes 17 instead of 35 us, the
+// humanoid 19 / 33, the quadruped at 64 samples 13 / 20.5, the arm 10 / 12.5, a
+// 16-robot round's 28 / 36.  It has more waves to start and more barriers, which
+// cost more than they save once the device is full: a 64-robot round's updates
+// (2 100 parts) took 130 us with 256 threads, so launches past kUpdWideParts parts
+// take 64.
 
-// Block-wide sum in a fixed order (tree over threads), deterministic.
+// Sum of x over threads 0 .. T-1 in a fixed order (a tree over threads).
 template <int T>
 __device__ __forceinline__ float block_sum(float x, float* buf) {
   const int t = threadIdx.x;
-  buf[t] = x;
-  __syncthreads();
-  for (int off = T / 2; off > 0; off >>= 1) {
-    if (t < off) buf[t] += buf[t + off];
+  if constexpr (T > 64) {
+    if (t < T) buf[t] = x;
     __syncthreads();
+#pragma unroll
+    for (int off = T / 2; off > 64; off >>= 1) {
+      if (t < off) buf[t] += buf[t + off];
+      __syncthreads();
+    }
+    if (t < 64) x = buf[t] + buf[t + 64];
   }
-  const float r = buf[0];
+  if (t < 64) {
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) x += __shfl_down(x, off, 64);  // lanes < off hold the tree's sums
+    if (t == 0) buf[T] = x;
+  }
   __syncthreads();
-  return r;
+  return buf[T];
 }
 
 // Sums over one index range of a row-major [*, E] array, V consecutive floats
-// (V = 4 or 1) per element block.  The workgroup covers up to T element blocks
-// at a time; G = T / min(T, blocks) thread groups take the rows in turn (group
-// g: rows g, g + G, ...), each in index order, and their sums are added in
-// group order.
+// (V = 4 or 1) per element block.
 template <int V>
 struct VecT;
 template <>
@@ -1435,28 +1450,27 @@ struct VecT<1> {
 };
 
 // sum_{n < cnt} w[n] rows[n][:] (w null: weight 1); the result goes to
-// emit(element block, value) on threads t < blocks in the chunk.  The element
-// blocks are taken NT at a time; each block's rows are split over G threads
-// (rows g, g + G, ...), whose sums are then added in g order.  G depends on the
-// number of blocks only (NT / EV, at least 1), not on the chunk, so every element
-// is added in the same order whichever chunk holds it.
-template <int V, int NT, typename Emit>
+// emit(element block, value).  Each block's rows are split over G groups (rows g,
+// g + G, ...), each in index order, whose sums are added in g order; G is what T
+// threads give (T / blocks, at least 1).  A thread takes one block of one group.
+template <int V, int T, int NT, typename Emit>
 __device__ __forceinline__ void rows_weighted_sum(const float* __restrict__ rows, int cnt, int E, const float* w,
-                                                  float* s_part, Emit emit) {
+                                                  float4* s_part, Emit emit) {
   using VT = VecT<V>;
-  using T = typename VT::T;
+  using F = typename VT::T;
+  constexpr int kIn = T == 64 ? 16 : 24;  // loads in flight per thread (rows past cnt are not loaded)
   const int t = threadIdx.x, EV = E / V;
-  T* part = reinterpret_cast<T*>(s_part);
-  const T* col = reinterpret_cast<const T*>(rows);
-  constexpr int kIn = 24;  // loads in flight per thread (rows past cnt are not loaded)
-  const int G = NT / min(NT, EV);
-  for (int e0 = 0; e0 < EV; e0 += NT) {
-    const int ec = min(NT, EV - e0);
+  F* part = reinterpret_cast<F*>(s_part);
+  const F* col = reinterpret_cast<const F*>(rows);
+  const int G = T / min(T, EV);
+  const int EC = NT / G;
+  for (int e0 = 0; e0 < EV; e0 += EC) {
+    const int ec = min(EC, EV - e0);
     const int el = t % ec, g = t / ec, e = e0 + el;
-    T acc = VT::zero();
+    F acc = VT::zero();
     if (g < G) {
       for (int n = g; n < cnt; n += kIn * G) {
-        T a[kIn];
+        F a[kIn];
 #pragma unroll
         for (int q = 0; q < kIn; ++q) {
           const int r = n + q * G;
@@ -1476,7 +1490,7 @@ __device__ __forceinline__ void rows_weighted_sum(const float* __restrict__ rows
     if (g < G) part[g * ec + el] = acc;
     __syncthreads();
     if (t < ec) {
-      T sum = VT::zero();
+      F sum = VT::zero();
       for (int k = 0; k < G; ++k) VT::add(part[k * ec + t], sum);
       emit(e0 + t, sum);
     }
@@ -1487,19 +1501,16 @@ __device__ __forceinline__ void rows_weighted_sum(const float* __restrict__ rows
 // with each sample's knots drawn again from the counter-based stream instead of
 // read (the rollout kernel then stores none).  Element block b holds positions
 // 2b, 2b + 1 and velocities 2b, 2b + 1 (one counter-based block); there are
-// E / 4 of them, as many as rows_weighted_sum<4> has, so the rows of every block
-// are split over as many threads (G), every element is accumulated over the same
-// rows in the same order and the two forms give the same bits (a block may sit
-// in another chunk of T blocks than in the stored form; G is the same for every
-// chunk).  Needs K nu even and the cubic Hermite knots (velocities sampled, not
-// derived).
+// E / 4 of them, as many as rows_weighted_sum<4> has, so every element's rows are
+// split over as many groups and added in the same order, and the two forms give
+// the same bits.  Needs K nu even and the cubic Hermite knots (velocities
+// sampled, not derived).  A workgroup of T threads: each draws the rows it adds.
 template <int T>
 __device__ __forceinline__ void regen_weighted_sum(const DevInst& I, const float* nom, uint32_t tick, int n0, int cnt,
-                                                   const float* w, float* s_part, float* mine) {
+                                                   const float* w, float4* part, float* mine) {
   const DevModel& M = *I.model;
   const int t = threadIdx.x, KU = I.K * I.nu, EV = KU / 2;
   const float* sig = I.sigma + I.iter * I.K;
-  float4* part = reinterpret_cast<float4*>(s_part);
   const int G = T / min(T, EV);
   for (int e0 = 0; e0 < EV; e0 += T) {
     const int ec = min(T, EV - e0);
@@ -1544,16 +1555,85 @@ __device__ __forceinline__ void regen_weighted_sum(const DevInst& I, const float
       mine[m] = sum.x; mine[m + 1] = sum.y;
       mine[KU + m] = sum.z; mine[KU + m + 1] = sum.w;
     }
+    __syncthreads();  // before the next blocks' sums
+  }
+}
+
+// The same for a workgroup of more threads: it draws a tile of rows of up to T
+// blocks into LDS (n_draws draws, T block constants), then thread g ec + el adds
+// block el's rows of group g.
+struct DrawConst {
+  float sq[2], lo[2], hi[2], nq[2], nv[2];
+};
+template <int T, int NT>
+__device__ __forceinline__ void regen_weighted_sum_tiles(const DevInst& I, const float* nom, uint32_t tick, int n0, int cnt,
+                                                   const float* w, float4* draws, int n_draws, DrawConst* consts,
+                                                   float* mine) {
+  const DevModel& M = *I.model;
+  const int t = threadIdx.x, KU = I.K * I.nu, EV = KU / 2;
+  const float* sig = I.sigma + I.iter * I.K;
+  const int G = T / min(T, EV);
+  for (int e0 = 0; e0 < EV; e0 += T) {
+    const int ec = min(T, EV - e0);
+    if (t < ec) {
+      DrawConst c;
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const int m = 2 * (e0 + t) + h;
+        const ElemConst e = elem_const(M, I, sig, m);
+        c.sq[h] = e.sq; c.lo[h] = e.lo; c.hi[h] = e.hi;
+        c.nq[h] = nom[m]; c.nv[h] = nom[KU + m];
+      }
+      consts[t] = c;
+    }
+    const int el = t % ec, g = t / ec;
+    float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+    const int RT = n_draws / ec;
+    for (int r0 = 0; r0 < cnt; r0 += RT) {
+      const int rt = min(RT, cnt - r0);
+      __syncthreads();  // the constants are there, the last tile has been added
+      for (int p = t; p < rt * ec; p += NT) {
+        const int r = p / ec, b = p % ec, n = n0 + r0 + r;
+        const DrawConst c = consts[b];
+        const uint4 x = sample_words(I, n, e0 + b, tick);
+        float4 th;
+        perturb_element(ElemConst{c.sq[0], c.lo[0], c.hi[0], 0}, I.delta, c.nq[0], c.nv[0], n, x.x, x.y, true, th.x, th.z);
+        perturb_element(ElemConst{c.sq[1], c.lo[1], c.hi[1], 0}, I.delta, c.nq[1], c.nv[1], n, x.z, x.w, true, th.y, th.w);
+        draws[p] = th;
+      }
+      __syncthreads();
+      if (g < G)
+        for (int r = r0 + (g + G - r0 % G) % G; r < r0 + rt; r += G) {
+          const float wr = w[r];
+          const float4 th = draws[(r - r0) * ec + el];
+          acc.x = fmaf(wr, th.x, acc.x); acc.y = fmaf(wr, th.y, acc.y);
+          acc.z = fmaf(wr, th.z, acc.z); acc.w = fmaf(wr, th.w, acc.w);
+        }
+    }
+    __syncthreads();
+    if (g < G) draws[g * ec + el] = acc;
+    __syncthreads();
+    if (t < ec) {
+      float4 sum = make_float4(0.f, 0.f, 0.f, 0.f);
+      for (int k = 0; k < G; ++k) {
+        const float4 a = draws[k * ec + t];
+        sum.x += a.x; sum.y += a.y; sum.z += a.z; sum.w += a.w;
+      }
+      const int m = 2 * (e0 + t);
+      mine[m] = sum.x; mine[m + 1] = sum.y;
+      mine[KU + m] = sum.z; mine[KU + m + 1] = sum.w;
+    }
+    __syncthreads();  // before the next blocks' constants and draws
   }
 }
 
 // Knots of sample n (drawn again, as above) into dst [E].
-template <int T>
+template <int NT>
 __device__ __forceinline__ void regen_sample(const DevInst& I, const float* nom, uint32_t tick, int n, float* dst) {
   const DevModel& M = *I.model;
   const int KU = I.K * I.nu;
   const float* sig = I.sigma + I.iter * I.K;
-  for (int b = threadIdx.x; b < KU / 2; b += T) {
+  for (int b = threadIdx.x; b < KU / 2; b += NT) {
     const uint4 x = sample_words(I, n, b, tick);
     float q0, v0, q1, v1;
     perturb_element(elem_const(M, I, sig, 2 * b), I.delta, nom[2 * b], nom[KU + 2 * b], n, x.x, x.y, true, q0, v0);
@@ -1566,7 +1646,7 @@ __device__ __forceinline__ void regen_sample(const DevInst& I, const float* nom,
 
 // The update of one instance by one workgroup (its part blockIdx.x); o: the
 // call's outputs (null fields: not wanted).
-template <int T>
+template <int T, int NT>
 __device__ __forceinline__ void update_body(const DevUpdate& U, const UpdateOut o) {
   const int part = blockIdx.x, parts = U.parts;
   if (part >= parts) return;
@@ -1575,72 +1655,70 @@ __device__ __forceinline__ void update_body(const DevUpdate& U, const UpdateOut 
   // iteration when the caller's buffer is read in place)
   const float* nom_in = o.nominal_in ? o.nominal_in : U.nominal_in;
   const uint32_t tick = U.regen ? sample_tick(*U.regen) : 0u;  // read before the last part advances it
-  __shared__ float s_v[T];
-  __shared__ int s_i[T];
-  __shared__ float s_x[T];
-  __shared__ __align__(16) float s_part[T * 4];
-  __shared__ int s_last;
+  // a tile of draws, or the groups' sums; the wide workgroup's costs in the same space
+  constexpr int kDraws = NT > T ? 1024 : T;
+  __shared__ __align__(16) float4 s_buf[kDraws];
+  __shared__ DrawConst s_const[NT > T ? T : 1];
   __shared__ float s_w[(65536 + kUpdMaxParts - 1) / kUpdMaxParts];  // this part's normalised weights (N <= 65536)
+  __shared__ float s_tree[T + 1], s_min[NT / 64], s_max[NT / 64];
+  __shared__ int s_arg[NT / 64], s_fin[NT / 64], s_last;
+  float* s_cost = reinterpret_cast<float*>(s_buf);
+  static_assert(NT == T || 4 * kDraws >= 1024, "the wide workgroup stages all costs (N <= 1024)");
 
   // this part's slice of the samples
   const int slice = (N + parts - 1) / parts;
   const int n0 = part * slice, cnt = max(0, min(N, n0 + slice) - n0);
 
   // 1. over all samples (every part the same way, so every part gets the same
-  //    values): finite minimum (lowest index), maximum and count.  Each thread
-  //    takes samples t, t + T, ... in order; up to kReg of them stay in
-  //    registers for the weight sum, and the slice's costs go to s_w.
-  constexpr int kIn = 8, kReg = 16;
-  const bool in_regs = N <= kReg * T;
+  //    values): finite minimum (lowest index), maximum and count
   const float* costs = U.costs;
-  float Sv[kReg];
   float mn = INFINITY, mx = -INFINITY;
   int arg = 0x7fffffff, nf = 0;
-  auto visit = [&](float S, int n) {
-    if (n >= n0 && n < n0 + cnt) s_w[n - n0] = S;
-    if (isfinite(S)) {
-      ++nf;
-      if (S < mn) { mn = S; arg = n; }
-      mx = fmaxf(mx, S);
-    }
-  };
-  if (in_regs) {
+  constexpr int kIn = NT > T ? 4 : 16;
+  for (int m0 = t; m0 < N; m0 += kIn * NT) {
+    float Sq[kIn];
 #pragma unroll
-    for (int q = 0; q < kReg; ++q) {
-      const int n = t + q * T;
-      Sv[q] = n < N ? costs[n] : INFINITY;
+    for (int q = 0; q < kIn; ++q) {
+      const int n = m0 + q * NT;
+      Sq[q] = n < N ? costs[n] : INFINITY;
     }
 #pragma unroll
-    for (int q = 0; q < kReg; ++q) visit(Sv[q], t + q * T);
-  } else {
-    for (int m0 = t; m0 < N; m0 += kIn * T) {
-      float Sq[kIn];
-#pragma unroll
-      for (int q = 0; q < kIn; ++q) {
-        const int n = m0 + q * T;
-        Sq[q] = n < N ? costs[n] : INFINITY;
+    for (int q = 0; q < kIn; ++q) {
+      const int n = m0 + q * NT;
+      const float S = Sq[q];
+      if constexpr (NT > T) {
+        if (n < N) s_cost[n] = S;
+      } else {
+        if (n >= n0 && n < n0 + cnt) s_w[n - n0] = S;  // the slice's costs
       }
+      if (isfinite(S)) {
+        ++nf;
+        if (S < mn) { mn = S; arg = n; }
+        mx = fmaxf(mx, S);
+      }
+    }
+  }
 #pragma unroll
-      for (int q = 0; q < kIn; ++q) visit(Sq[q], m0 + q * T);
-    }
+  for (int off = 32; off > 0; off >>= 1) {
+    const float om = __shfl_xor(mn, off, 64), ox = __shfl_xor(mx, off, 64);
+    const int oi = __shfl_xor(arg, off, 64), of = __shfl_xor(nf, off, 64);
+    if (om < mn || (om == mn && oi < arg)) { mn = om; arg = oi; }
+    mx = fmaxf(mx, ox);
+    nf += of;
   }
-  s_v[t] = mn; s_i[t] = arg; s_x[t] = mx;
+  if (t % 64 == 0) { s_min[t / 64] = mn; s_max[t / 64] = mx; s_arg[t / 64] = arg; s_fin[t / 64] = nf; }
   __syncthreads();
-  for (int off = T / 2; off > 0; off >>= 1) {
-    if (t < off) {
-      const float om = s_v[t + off];
-      const int oi = s_i[t + off];
-      if (om < s_v[t] || (om == s_v[t] && oi < s_i[t])) { s_v[t] = om; s_i[t] = oi; }
-      s_x[t] = fmaxf(s_x[t], s_x[t + off]);
-    }
-    __syncthreads();
+  float smin = s_min[0], smax = s_max[0];
+  int nstar = s_arg[0], nfin = s_fin[0];
+#pragma unroll
+  for (int k = 1; k < NT / 64; ++k) {
+    if (s_min[k] < smin || (s_min[k] == smin && s_arg[k] < nstar)) { smin = s_min[k]; nstar = s_arg[k]; }
+    smax = fmaxf(smax, s_max[k]);
+    nfin += s_fin[k];
   }
-  const float smin = s_v[0], smax = s_x[0];
-  const int nstar = s_i[0];
-  __syncthreads();
-  const int nfin = (int)block_sum<T>((float)nf, s_x);
 
-  // 2. unnormalised weights e_n = exp(-S_hat / lambda) and their sum
+  // 2. unnormalised weights e_n = exp(-S_hat / lambda) and their sum: thread t < T
+  //    adds samples t, t + T, ... in order, then a tree over the T threads
   const float range = smax - smin;
   const float inv_range = (U.weight_mode == 0 && range > 0.f) ? 1.f / range : 0.f;
   const float inv_lam = 1.f / U.lambda;
@@ -1650,125 +1728,127 @@ __device__ __forceinline__ void update_body(const DevUpdate& U, const UpdateOut 
     return expf(-sh * inv_lam);
   };
   float zs = 0.f;
-  if (in_regs) {
-#pragma unroll
-    for (int q = 0; q < kReg; ++q) zs += weight(Sv[q]);
+  if constexpr (NT > T) {
+    for (int i = t; i < N; i += NT) s_cost[i] = weight(s_cost[i]);
+    __syncthreads();
+    if (t < T)
+      for (int i = t; i < N; i += T) zs += s_cost[i];
   } else {
-    for (int m0 = t; m0 < N; m0 += kIn * T) {
+    for (int m0 = t; m0 < N; m0 += kIn * NT) {
       float Sq[kIn];
 #pragma unroll
       for (int q = 0; q < kIn; ++q) {
-        const int n = m0 + q * T;
+        const int n = m0 + q * NT;
         Sq[q] = n < N ? costs[n] : INFINITY;
       }
 #pragma unroll
       for (int q = 0; q < kIn; ++q) zs += weight(Sq[q]);
     }
   }
-  const float Z = block_sum<T>(zs, s_x);
+  const float Z = block_sum<T>(zs, s_tree);
   const float invZ = nfin > 0 ? 1.f / Z : 0.f;
 
-  // 3. this part's slice: normalised weights (from the costs in s_w), then its
-  //    weighted knot sum
-  for (int i = t; i < cnt; i += T) {
-    const float w = weight(s_w[i]) * invZ;
+  // 3. this part's slice: normalised weights, then its weighted knot sum
+  for (int i = t; i < cnt; i += NT) {
+    const float w = (NT > T ? s_cost[n0 + i] : weight(s_w[i])) * invZ;
     s_w[i] = w;
     if (U.weights) U.weights[n0 + i] = w;
   }
   __syncthreads();
   float* mine = U.partial + (size_t)part * E;
-  if (U.regen)
-    regen_weighted_sum<T>(*U.regen, nom_in, tick, n0, cnt, s_w, s_part, mine);
-  else if ((E & 3) == 0)
-    rows_weighted_sum<4, T>(U.samples + (size_t)n0 * E, cnt, E, s_w, s_part,
-                         [&](int e, float4 v) { reinterpret_cast<float4*>(mine)[e] = v; });
+  if (U.regen) {
+    if constexpr (NT > T) regen_weighted_sum_tiles<T, NT>(*U.regen, nom_in, tick, n0, cnt, s_w, s_buf, kDraws, s_const, mine);
+    else regen_weighted_sum<T>(*U.regen, nom_in, tick, n0, cnt, s_w, s_buf, mine);
+  } else if ((E & 3) == 0)
+    rows_weighted_sum<4, T, NT>(U.samples + (size_t)n0 * E, cnt, E, s_w, s_buf,
+                            [&](int e, float4 v) { reinterpret_cast<float4*>(mine)[e] = v; });
   else
-    rows_weighted_sum<1, T>(U.samples + (size_t)n0 * E, cnt, E, s_w, s_part, [&](int e, float v) { mine[e] = v; });
+    rows_weighted_sum<1, T, NT>(U.samples + (size_t)n0 * E, cnt, E, s_w, s_buf, [&](int e, float v) { mine[e] = v; });
 
   // 4. the last part to finish adds the slices in part order
-  __threadfence();
-  __syncthreads();
-  if (t == 0) s_last = atomicAdd(U.done, 1u) == (uint32_t)(parts - 1);
-  __syncthreads();
-  if (!s_last) return;
-  __threadfence();
-  if (t == 0) U.done[0] = 0u;  // ready for the next launch
-  float* dst = (U.last_iter && o.knots_out) ? o.knots_out : U.nominal_out;
-  // the call's running best starts from its input nominal; the best tracking
-  // runs before the nominal output is written, since the two may be the same
-  // buffer and a drawn-again best sample reads the input nominal
-  float* bs = U.best_state;  // [E] knots, then S_best, best_iter, n_nonfinite, all_nonfinite, best_sample
-  if (U.first_iter) {
-    for (int e = t; e < E; e += T) bs[e] = nom_in[e];
+  if (parts > 1) {
+    // one fence per workgroup, after all its threads' sums are written: each
+    // device-scope fence writes back the XCD's L2
+    __syncthreads();
     if (t == 0) {
-      bs[E] = INFINITY;
-      reinterpret_cast<int*>(bs)[E + 1] = -1;
-      reinterpret_cast<int*>(bs)[E + 2] = 0;
-      reinterpret_cast<int*>(bs)[E + 3] = 0;
-      reinterpret_cast<int*>(bs)[E + 4] = -1;
+      __threadfence();
+      s_last = atomicAdd(U.done, 1u) == (uint32_t)(parts - 1);
     }
+    __syncthreads();
+    if (!s_last) return;
+    __threadfence();
+    if (t == 0) U.done[0] = 0u;  // ready for the next launch
   }
   __syncthreads();
+  float* dst = (U.last_iter && o.knots_out) ? o.knots_out : U.nominal_out;
 
-  // 5. best-sample tracking across the iterations of this call
-  const bool improve = nfin > 0 && U.costs[nstar] < bs[E];
-  __syncthreads();
-  if (improve) {
-    if (U.regen) regen_sample<T>(*U.regen, nom_in, tick, nstar, bs);
-    else
-      for (int e = t; e < E; e += T) bs[e] = U.samples[(size_t)nstar * E + e];
+  // 5. best-sample tracking across the iterations of this call, whose running best
+  //    starts from its input nominal.  It reads the nominal before the output is
+  //    written, since the two may be the same buffer.
+  float* bs = U.best_state;  // [E] knots, then S_best, best_iter, n_nonfinite, all_nonfinite, best_sample
+  int* bi = reinterpret_cast<int*>(bs);
+  const bool first = U.first_iter;
+  float S_best = INFINITY;
+  int best_iter = -1, best_sample = -1, nonfinite = 0, all_nonfinite = 0;
+  if (!first) {
+    S_best = bs[E];
+    best_iter = bi[E + 1]; nonfinite = bi[E + 2]; all_nonfinite = bi[E + 3]; best_sample = bi[E + 4];
   }
-  __syncthreads();
+  const bool improve = nfin > 0 && smin < S_best;
+  if (improve) { S_best = smin; best_iter = U.iter; best_sample = nstar; }
+  nonfinite += N - nfin;
+  all_nonfinite += nfin == 0 ? 1 : 0;
+  __syncthreads();  // every thread has read the running best
+  if (improve) {
+    if (U.regen) regen_sample<NT>(*U.regen, nom_in, tick, nstar, bs);
+    else
+      for (int e = t; e < E; e += NT) bs[e] = U.samples[(size_t)nstar * E + e];
+  } else if (first) {
+    for (int e = t; e < E; e += NT) bs[e] = nom_in[e];
+  }
   if (t == 0) {
-    if (improve) {
-      bs[E] = U.costs[nstar];
-      reinterpret_cast<int*>(bs)[E + 1] = U.iter;
-      reinterpret_cast<int*>(bs)[E + 4] = nstar;
-    }
-    reinterpret_cast<int*>(bs)[E + 2] += N - nfin;
-    reinterpret_cast<int*>(bs)[E + 3] += nfin == 0 ? 1 : 0;
+    bs[E] = S_best;
+    bi[E + 1] = best_iter; bi[E + 2] = nonfinite; bi[E + 3] = all_nonfinite; bi[E + 4] = best_sample;
   }
   __syncthreads();
 
   // 6. the nominal: the slices added in part order
   if ((E & 3) == 0)
-    rows_weighted_sum<4, T>(U.partial, parts, E, nullptr, s_part, [&](int e, float4 v) {
+    rows_weighted_sum<4, T, NT>(U.partial, parts, E, nullptr, s_buf, [&](int e, float4 v) {
       const float c[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
       for (int k = 0; k < 4; ++k) dst[4 * e + k] = nfin > 0 ? c[k] : nom_in[4 * e + k];
     });
   else
-    rows_weighted_sum<1, T>(U.partial, parts, E, nullptr, s_part,
-                         [&](int e, float v) { dst[e] = nfin > 0 ? v : nom_in[e]; });
+    rows_weighted_sum<1, T, NT>(U.partial, parts, E, nullptr, s_buf, [&](int e, float v) { dst[e] = nfin > 0 ? v : nom_in[e]; });
   __syncthreads();
   if (U.last_iter) {
     if (o.best_out)
-      for (int e = t; e < E; e += T) o.best_out[e] = bs[e];
+      for (int e = t; e < E; e += NT) o.best_out[e] = bs[e];
     if (t == 0 && o.info_out) {
       float* inf = reinterpret_cast<float*>(o.info_out);
-      inf[0] = bs[E];
-      reinterpret_cast<int*>(inf)[1] = reinterpret_cast<int*>(bs)[E + 1];
-      reinterpret_cast<int*>(inf)[2] = reinterpret_cast<int*>(bs)[E + 2];
-      reinterpret_cast<int*>(inf)[3] = reinterpret_cast<int*>(bs)[E + 3];
-      reinterpret_cast<int*>(inf)[4] = reinterpret_cast<int*>(bs)[E + 4];
+      int* ii = reinterpret_cast<int*>(o.info_out);
+      inf[0] = S_best;
+      ii[1] = best_iter; ii[2] = nonfinite; ii[3] = all_nonfinite; ii[4] = best_sample;
     }
   }
   if (U.last_iter && t == 0 && U.tick) U.tick[0] += 1u;
 }
 
-template <int T>
-__global__ __launch_bounds__(T) void update_kernel(const DevUpdate* __restrict__ ups,
-                                                   const UpdateOut* __restrict__ outs, UpdateOut single) {
-  update_body<T>(ups[blockIdx.y], outs ? outs[blockIdx.y] : single);
+template <int T, int NT>
+__global__ __launch_bounds__(NT) void update_kernel(const DevUpdate* __restrict__ ups,
+                                                    const UpdateOut* __restrict__ outs, UpdateOut single) {
+  update_body<T, NT>(ups[blockIdx.y], outs ? outs[blockIdx.y] : single);
 }
 
 // One instance whose descriptor arrives as a kernel argument (no device copy of
 // it), with no per-call outputs besides the nominal and the weights.
 __global__ __launch_bounds__(kUpdThreads) void update_single_kernel(DevUpdate U) {
-  update_body<kUpdThreads>(U, UpdateOut{nullptr, nullptr, nullptr, nullptr});
+  update_body<kUpdThreads, kUpdThreads>(U, UpdateOut{nullptr, nullptr, nullptr, nullptr});
 }
-template __global__ void update_kernel<64>(const DevUpdate*, const UpdateOut*, UpdateOut);
-template __global__ void update_kernel<256>(const DevUpdate*, const UpdateOut*, UpdateOut);
+template __global__ void update_kernel<64, 64>(const DevUpdate*, const UpdateOut*, UpdateOut);
+template __global__ void update_kernel<64, 256>(const DevUpdate*, const UpdateOut*, UpdateOut);
+template __global__ void update_kernel<256, 256>(const DevUpdate*, const UpdateOut*, UpdateOut);
 
 // Warm start (Sec. III-E): the knots of a trajectory shifted forward by n_steps
 // control steps, i.e. its spline at t_k + n_steps dt clamped to the horizon end
