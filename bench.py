@@ -59,7 +59,7 @@ def _pct(xs, q):
 
 def kernel_source_digest():
     h = hashlib.sha256()
-    for f in ("mppi_kernels.hip", "mppi_dev.hpp"):
+    for f in ("mppi_kernels.hip", "mppi_paths.hip", "mppi_path.hpp", "mppi_lane.hpp", "mppi_step.hpp", "mppi_dev.hpp"):
         h.update(open(os.path.join(ROOT, "paper_2511_19204_amd", "csrc", f), "rb").read())
     return h.hexdigest()[:16]
 
@@ -85,8 +85,10 @@ def measured_traffic(digest):
 
 def kernel_label(m, schedule, lanes):
     """Name of the rollout kernel instance the library launches for model m: the
-    body and team kernels are specialised on tree depth (at most 3 or 6 levels
-    below the root, else the generic loop, 0)."""
+    body schedule at its default lane count takes the path kernel where the tree's
+    root-to-leaf paths fit it (at most 8, of at most 6 bodies); the body and team
+    kernels are specialised on tree depth (at most 3 or 6 levels below the root,
+    else the generic loop, 0)."""
     par = [int(x) for x in m["parent"]]
     depth = []
     for i, lam in enumerate(par):
@@ -95,6 +97,9 @@ def kernel_label(m, schedule, lanes):
     spec = 3 if d <= 3 else 6 if d <= 6 else 0
     if schedule == "chain":
         return f"chain_kernel<{lanes}>"
+    leaves = sum(1 for b in range(len(par)) if b not in par)
+    if schedule == "body" and lanes == 1 << max(2, (len(par) - 1).bit_length()) and leaves <= 8 and d <= 6:
+        return "path_kernel"
     if schedule == "team":
         return f"team_kernel<{lanes}, {spec}>"
     # legged trees (a floating base with serial chains, depth first) up to three

@@ -174,6 +174,11 @@ mppi_status mppi_get_tick(const mppi_ctx* c, uint32_t* tick);
  * one rollout (the articulated-body sweeps of the forward dynamics).
  *   MPPI_SCHEDULE_BODY   one lane per body; the tree is swept level by level,
  *                        lanes per rollout = a power of two 4..64 >= n_bodies.
+ *                        At the smallest such count, and where the tree has at
+ *                        most 8 root-to-leaf paths of at most 6 bodies, launches
+ *                        share a rollout by path instead (four lanes or one to
+ *                        each path, by the size of the launch), bit for bit the
+ *                        same; persistent launches keep one lane per body.
  *   MPPI_SCHEDULE_CHAIN  one lane per kinematic chain of the tree's heavy-path
  *                        decomposition (a body continues its parent's chain when
  *                        it heads the parent's largest subtree); each lane walks

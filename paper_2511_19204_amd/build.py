@@ -10,7 +10,8 @@ The compiler's per-kernel resource remarks are checked: no kernel may use
 scratch memory (register spills), and the body-schedule rollout kernel and every
 persistent kernel must fit two wavefronts per SIMD (at most 256 VGPRs), which
 launches of more than one wavefront per SIMD rely on (the persistent forms size
-their grids to the occupancy they get).
+their grids to the occupancy they get).  The path kernel holds one wavefront per SIMD
+with all 512 registers and launches for that.
 """
 import os
 import re

@@ -1,4 +1,6 @@
-// mppi_kernels.hip -- gfx950 kernels of the MPPI hot path.
+// mppi_kernels.hip -- gfx950 kernels of the MPPI hot path: the body, chain and
+// team schedules' rollouts and the update.  Launches at the body schedule's default
+// lane count run the path kernel (mppi_paths.hip) where it takes the tree.
 //
 // Rollout kernel: G lanes per rollout (G in {4, 8, 16, 32, 64}), 64/G
 // rollouts per wavefront, one lane per rigid body (= one actuated joint).
@@ -11,7 +13,7 @@
 // contact, articulated-body forward dynamics, running cost (Sec. IV-A) and a
 // linearly implicit Euler step, and finally the terminal cost.
 //
-// Update kernel: one workgroup per instance; min / max / argmin of the costs,
+// Update kernel: a few workgroups per instance, each a slice of its samples; min / max / argmin of the costs,
 // min-max normalised softmax weights (eq. softmax_minmax; eq. omega-weights in
 // raw mode), the weighted knot average (eq. update-nominal carried to the
 // knots) and best-sample tracking (Sec. III-D).  Every reduction runs in a
@@ -1396,12 +1398,12 @@ __global__ void reset_counters(unsigned int* __restrict__ c, int n) {
 // T threads draws each element block's rows in the block's own thread.  At T = 64
 // a workgroup of NT = 256 shares what has no order -- the statistics, the weights
 // and, above all, the draws of a slice's samples, about 330 instructions each --
-// and so ends sooner: an update of the hexapod takes 17 instead of 35 us, the
+// and so ends sooner: an update of the hexapod takes 16 instead of 35 us, the
 // humanoid 19 / 33, the quadruped at 64 samples 13 / 20.5, the arm 10 / 12.5, a
-// 16-robot round's 28 / 36.  It has more waves to start and more barriers, which
+// 16-robot round's 27 / 36.  It has more waves to start and more barriers, which
 // cost more than they save once the device is full: a 64-robot round's updates
-// (2 100 parts) took 130 us with 256 threads, so launches past kUpdWideParts parts
-// take 64.
+// (2 100 parts) take 130 us with 256 threads and 80 with 64, so launches of more
+// than kUpdWideParts parts take 64.
 
 // Sum of x over threads 0 .. T-1 in a fixed order (a tree over threads).
 template <int T>

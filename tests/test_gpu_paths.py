@@ -230,3 +230,37 @@ def test_mixed_batch_equals_plain_steps(scale):
     for i, a in enumerate(plain):
         for k, t in (("knots", ko[i]), ("best", best[i]), ("info", info[i])):
             assert np.array_equal(a[k], t.cpu().numpy(), equal_nan=True), (names[i], k)
+
+
+@pytest.mark.parametrize("copies,sizes", [(8, (1, 15, 16, 17, 63, 64, 65, 1008, 1024, 1025)), (2, (1000, 1023, 1025, 4097))])
+@pytest.mark.parametrize("knots", [4, 5])
+def test_update_forms_agree(copies, sizes, knots):
+    """The update's 64-wide sums from workgroups of 256 threads (an instance alone) and
+    of 64 (a launch of more than 1024 parts): sizes around a slice of 16 samples, the
+    last slice and the width's limit of 1024 samples, an odd and an even number of
+    knot elements (stored samples and samples drawn again)."""
+    m = TREES["arm"]()
+    ps = [_params(m, n, horizon=2, knots=knots, iters=2) for n in sizes] * copies
+    parts = sum((p["n_samples"] + 15) // 16 for p in ps if p["n_samples"] <= 1024)
+    model = mppi.Model(m)
+    x = torch.tensor(np.asarray(m["x0"], np.float32), device="cuda")
+    ctrls = [mppi.Controller(model, p, 3 + i) for i, p in enumerate(ps)]
+    kn = torch.tensor(np.asarray(synth.nominal_knots(m, knots), np.float32), device="cuda")
+    out = {}
+    for form in ("alone", "batch"):
+        ko = [torch.zeros(c.E, device="cuda") for c in ctrls]
+        best = [torch.zeros(c.E, device="cuda") for c in ctrls]
+        info = [torch.zeros(mppi.INFO_INTS, dtype=torch.int32, device="cuda") for _ in ctrls]
+        for c in ctrls:
+            c.tick = 0
+        if form == "alone":
+            for i, c in enumerate(ctrls):
+                c.step(x, kn, ko[i], best[i], info[i])
+        else:
+            mppi.step_batch(ctrls, [x] * len(ctrls), [kn] * len(ctrls), ko, best, info)
+        torch.cuda.synchronize()
+        out[form] = [[t.cpu().numpy() for t in ts] for ts in zip(ko, best, info)]
+    assert (parts > 1024) == (copies == 8), parts
+    for p, a, b in zip(ps, out["alone"], out["batch"]):
+        for s, t in zip(a, b):
+            assert np.array_equal(s, t, equal_nan=True), p["n_samples"]
