@@ -49,7 +49,7 @@ __global__ void shift_knots_kernel(const float*, float*, int, int, int, int, int
 template <int G>
 __global__ void dynamics_kernel(const DevModel*, int, const float*, const float*, const float*, const float*, float,
                                 float*, int, int);
-template <int T, int NT> __global__ void update_kernel(const DevUpdate*, const UpdateOut*, UpdateOut);
+template <int T> __global__ void update_kernel(const DevUpdate*, const UpdateOut*, UpdateOut, int);
 __global__ void update_single_kernel(DevUpdate);
 __global__ void set_targets_kernel(DevTargets*, DevTargets);
 struct StageItem {
@@ -120,7 +120,7 @@ struct mppi_ctx {
   DevInst* d_pred_inst = nullptr;
   uint32_t* tick = nullptr;
   float* upd_partial = nullptr;  // [update_shape(N).parts][E] update scratch
-  uint32_t* upd_done = nullptr;  // update parts finished (0 between launches)
+  uint32_t* upd_done = nullptr;  // [1 + kUpdMaxChunks] update workgroups finished (0 between launches)
   DevInst* d_insts = nullptr;   // [I]
   DevUpdate* d_ups = nullptr;   // [I]
   std::vector<DevInst> h_insts;
@@ -660,7 +660,8 @@ extern "C" mppi_status mppi_create(const mppi_model* m, const mppi_params* p, ui
   if ((e = hipMalloc(&c->tick, sizeof(uint32_t))) != hipSuccess) return bail(e, "hipMalloc tick");
   if ((e = hipMalloc(&c->upd_partial, (size_t)update_shape(c->N).parts * E * sizeof(float))) != hipSuccess)
     return bail(e, "hipMalloc update scratch");
-  if ((e = hipMalloc(&c->upd_done, sizeof(uint32_t))) != hipSuccess) return bail(e, "hipMalloc update counter");
+  if ((e = hipMalloc(&c->upd_done, (1 + kUpdMaxChunks) * sizeof(uint32_t))) != hipSuccess)
+    return bail(e, "hipMalloc update counters");
   if ((e = hipMalloc(&c->d_insts, c->I * sizeof(DevInst))) != hipSuccess) return bail(e, "hipMalloc insts");
   if ((e = hipMalloc(&c->d_ups, c->I * sizeof(DevUpdate))) != hipSuccess) return bail(e, "hipMalloc ups");
   if ((e = hipMalloc(&c->d_targets, sizeof(DevTargets))) != hipSuccess) return bail(e, "hipMalloc targets");
@@ -679,8 +680,9 @@ extern "C" mppi_status mppi_create(const mppi_model* m, const mppi_params* p, ui
   if ((e = hipMemcpy(c->f0z, f0.data(), f0.size() * sizeof(float), hipMemcpyHostToDevice)) != hipSuccess) return bail(e, "upload f0z");
   if ((e = hipMemcpy(c->q0, q0.data(), q0.size() * sizeof(float), hipMemcpyHostToDevice)) != hipSuccess) return bail(e, "upload q0");
   if ((e = hipMemcpy(c->tick, &zero, sizeof(uint32_t), hipMemcpyHostToDevice)) != hipSuccess) return bail(e, "upload tick");
-  if ((e = hipMemcpy(c->upd_done, &zero, sizeof(uint32_t), hipMemcpyHostToDevice)) != hipSuccess)
-    return bail(e, "upload update counter");
+  const uint32_t zeros[1 + kUpdMaxChunks] = {};
+  if ((e = hipMemcpy(c->upd_done, zeros, sizeof(zeros), hipMemcpyHostToDevice)) != hipSuccess)
+    return bail(e, "upload update counters");
   if ((e = hipMalloc(&c->x_meas, (c->nq + c->nv) * sizeof(float))) != hipSuccess) return bail(e, "hipMalloc x_meas");
   if ((e = hipMalloc(&c->pred_knots, E * sizeof(float))) != hipSuccess) return bail(e, "hipMalloc pred knots");
   if ((e = hipMalloc(&c->pred_cost, sizeof(float))) != hipSuccess) return bail(e, "hipMalloc pred cost");
@@ -1172,12 +1174,17 @@ static std::atomic<int> g_persistent{0};
 // parts, then n256 of at most parts256.
 struct UpdGrid {
   int n64 = 0, parts64 = 1, n256 = 0, parts256 = 1;
-  int all64 = 0;  // parts of the 64-thread updates together
+  // workgroups of the 64-thread updates with tiles of kUpdTile >> k blocks: together, of one
+  int all[3] = {}, most[3] = {1, 1, 1};
   void add(const DevUpdate& u) {
     if (u.threads == 64) {
       ++n64;
-      all64 += u.parts;
       parts64 = std::max(parts64, u.parts);
+      for (int k = 0; k < 3; ++k) {
+        const int b = u.regen ? u.parts * update_chunks(u.E / 4, kUpdTile >> k) : u.parts;
+        all[k] += b;
+        most[k] = std::max(most[k], b);
+      }
     } else {
       ++n256;
       parts256 = std::max(parts256, u.parts);
@@ -1190,19 +1197,27 @@ static void order_by_update_shape(std::vector<int>& idx, const std::function<int
 }
 static hipError_t launch_updates(const DevUpdate* ups, const UpdateOut* outs, const UpdGrid& g, hipStream_t s) {
   const UpdateOut none{nullptr, nullptr, nullptr, nullptr};
-  if (g.n64 > 0 && g.all64 <= kUpdWideParts)
-    hipLaunchKernelGGL((update_kernel<64, 256>), dim3(g.parts64, g.n64), dim3(256), 0, s, ups, outs, none);
-  else if (g.n64 > 0)
-    hipLaunchKernelGGL((update_kernel<64, 64>), dim3(g.parts64, g.n64), dim3(64), 0, s, ups, outs, none);
+  int k = -1;  // the narrowest tiles (8 blocks at least) of kUpdSpread workgroups at most, else whole parts
+  for (int j = 0; j < 3; ++j)
+    if (g.all[j] <= kUpdSpread) k = j;
+  if (g.n64 > 0)
+    hipLaunchKernelGGL(update_kernel<64>, dim3(k < 0 ? g.parts64 : g.most[k], g.n64), dim3(64), 0, s, ups, outs, none,
+                       k < 0 ? 0 : kUpdTile >> k);
   if (g.n256 > 0)
-    hipLaunchKernelGGL((update_kernel<256, 256>), dim3(g.parts256, g.n256), dim3(256), 0, s, ups + g.n64,
-                       outs ? outs + g.n64 : nullptr, none);
+    hipLaunchKernelGGL(update_kernel<kUpdThreads>, dim3(g.parts256, g.n256), dim3(kUpdThreads), 0, s, ups + g.n64,
+                       outs ? outs + g.n64 : nullptr, none, 0);
   return hipGetLastError();
 }
 // one instance's update (its shape), with the call's outputs o
 static hipError_t launch_update1(const DevUpdate* u, const DevUpdate& h, const UpdateOut& o, hipStream_t s) {
-  if (h.threads == 64) hipLaunchKernelGGL((update_kernel<64, 256>), dim3(h.parts, 1), dim3(256), 0, s, u, nullptr, o);
-  else hipLaunchKernelGGL((update_kernel<256, 256>), dim3(h.parts, 1), dim3(256), 0, s, u, nullptr, o);
+  // one instance: the narrowest tiles of 256 workgroups at most
+  int tile = kUpdTile;
+  while (tile > 4 && h.parts * update_chunks(h.E / 4, tile / 2) <= 256) tile /= 2;
+  if (h.threads == 64)
+    hipLaunchKernelGGL(update_kernel<64>, dim3(h.regen ? h.parts * update_chunks(h.E / 4, tile) : h.parts), dim3(64), 0, s, u,
+                       nullptr, o, tile);
+  else
+    hipLaunchKernelGGL(update_kernel<kUpdThreads>, dim3(h.parts), dim3(kUpdThreads), 0, s, u, nullptr, o, 0);
   return hipGetLastError();
 }
 

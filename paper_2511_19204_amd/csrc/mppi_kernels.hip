@@ -1393,17 +1393,23 @@ __global__ void reset_counters(unsigned int* __restrict__ c, int n) {
 // out (per call): the final nominal, best knots and info of the last iteration.
 // ---------------------------------------------------------------------------
 
-// T (64 or 256, update_shape) is the width of the sums' order: the weight sum and
-// a slice's knot sums are taken as T threads would take them.  A workgroup of NT =
-// T threads draws each element block's rows in the block's own thread.  At T = 64
-// a workgroup of NT = 256 shares what has no order -- the statistics, the weights
-// and, above all, the draws of a slice's samples, about 330 instructions each --
-// and so ends sooner: an update of the hexapod takes 16 instead of 35 us, the
-// humanoid 19 / 33, the quadruped at 64 samples 13 / 20.5, the arm 10 / 12.5, a
-// 16-robot round's 27 / 36.  It has more waves to start and more barriers, which
-// cost more than they save once the device is full: a 64-robot round's updates
-// (2 100 parts) take 130 us with 256 threads and 80 with 64, so launches of more
-// than kUpdWideParts parts take 64.
+// T (64 or 256, update_shape) is the workgroup's size and the width of the sums'
+// order.  An update is bound by latency: the draws of a slice's samples, about 330
+// instructions each (at T = 64 one thread per element block drew all 16 of its
+// rows, one after another), the statistics' chains and the hand-over to the part
+// that finishes last.  So at T = 64 a part is spread over workgroups of `tile`
+// element blocks, each of which forms the statistics and weights for itself and
+// draws its tile with all lanes; reductions are shuffles; the sums are stored
+// through to memory, so that no workgroup needs a fence (a device-scope fence
+// writes back the XCD's L2: with one per workgroup a 64-robot round's updates in
+// tiles of 32 blocks took 236 us, without 57).  One update before / now: hexapod
+// 35 / 14.6 us, humanoid 33 / 17.5, quadruped at 64 samples 20.5 / 12.2, at 4 096
+// (T = 256) 27.5 / 22.8, arm 12.5 / 11.9; a 16-robot round's 36 / 23.3, a 64-robot
+// round's 80 / 55.  The workgroups at T = 64 stay single wavefronts: one finds room
+// wherever a rollout wavefront has ended, while one of four waits until all SIMDs of
+// a compute unit are free at once (256 threads sharing the draws were as fast on an
+// idle device, but 64 served robots on six streams answered in 3.9 ms p50 / 12 ms
+// p99, with single wavefronts in 2.1 / 7.8).
 
 // Sum of x over threads 0 .. T-1 in a fixed order (a tree over threads).
 template <int T>
@@ -1427,6 +1433,14 @@ __device__ __forceinline__ float block_sum(float x, float* buf) {
   __syncthreads();
   return buf[T];
 }
+
+// A part's sums are read by the workgroup that finishes last, on any XCD: stored
+// through to memory (agent scope), so that publishing them takes a wait for the
+// stores and no fence, which would write back the XCD's whole L2.
+__device__ __forceinline__ void store_agent(float* p, float v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void wait_stores() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
 // Sums over one index range of a row-major [*, E] array, V consecutive floats
 // (V = 4 or 1) per element block.
@@ -1455,7 +1469,7 @@ struct VecT<1> {
 // emit(element block, value).  Each block's rows are split over G groups (rows g,
 // g + G, ...), each in index order, whose sums are added in g order; G is what T
 // threads give (T / blocks, at least 1).  A thread takes one block of one group.
-template <int V, int T, int NT, typename Emit>
+template <int V, int T, typename Emit>
 __device__ __forceinline__ void rows_weighted_sum(const float* __restrict__ rows, int cnt, int E, const float* w,
                                                   float4* s_part, Emit emit) {
   using VT = VecT<V>;
@@ -1465,7 +1479,7 @@ __device__ __forceinline__ void rows_weighted_sum(const float* __restrict__ rows
   F* part = reinterpret_cast<F*>(s_part);
   const F* col = reinterpret_cast<const F*>(rows);
   const int G = T / min(T, EV);
-  const int EC = NT / G;
+  const int EC = T / G;
   for (int e0 = 0; e0 < EV; e0 += EC) {
     const int ec = min(EC, EV - e0);
     const int el = t % ec, g = t / ec, e = e0 + el;
@@ -1554,64 +1568,54 @@ __device__ __forceinline__ void regen_weighted_sum(const DevInst& I, const float
         sum.x += a.x; sum.y += a.y; sum.z += a.z; sum.w += a.w;
       }
       const int m = 2 * (e0 + t);
-      mine[m] = sum.x; mine[m + 1] = sum.y;
-      mine[KU + m] = sum.z; mine[KU + m + 1] = sum.w;
+      store_agent(mine + m, sum.x); store_agent(mine + m + 1, sum.y);
+      store_agent(mine + KU + m, sum.z); store_agent(mine + KU + m + 1, sum.w);
     }
     __syncthreads();  // before the next blocks' sums
   }
 }
 
-// The same for a workgroup of more threads: it draws a tile of rows of up to T
-// blocks into LDS (n_draws draws, T block constants), then thread g ec + el adds
-// block el's rows of group g.
+// The same at T = 64 (slices of at most kUpdTileRows samples) for block tiles chunk,
+// chunk + chunks, ... of `tile` blocks (at most kUpdTile): the wavefront draws a
+// tile's samples into LDS, all lanes at work whatever the number of blocks, then
+// thread g ec + el adds block el's rows of group g.
 struct DrawConst {
-  float sq[2], lo[2], hi[2], nq[2], nv[2];
+  float sq, lo, hi, nq, nv;
 };
-template <int T, int NT>
 __device__ __forceinline__ void regen_weighted_sum_tiles(const DevInst& I, const float* nom, uint32_t tick, int n0, int cnt,
-                                                   const float* w, float4* draws, int n_draws, DrawConst* consts,
-                                                   float* mine) {
+                                                         const float* w, float4* draws, DrawConst* consts, float* mine,
+                                                         int tile, int chunk, int chunks) {
   const DevModel& M = *I.model;
   const int t = threadIdx.x, KU = I.K * I.nu, EV = KU / 2;
   const float* sig = I.sigma + I.iter * I.K;
-  const int G = T / min(T, EV);
-  for (int e0 = 0; e0 < EV; e0 += T) {
-    const int ec = min(T, EV - e0);
-    if (t < ec) {
-      DrawConst c;
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const int m = 2 * (e0 + t) + h;
-        const ElemConst e = elem_const(M, I, sig, m);
-        c.sq[h] = e.sq; c.lo[h] = e.lo; c.hi[h] = e.hi;
-        c.nq[h] = nom[m]; c.nv[h] = nom[KU + m];
-      }
-      consts[t] = c;
+  const int G = 64 / min(64, EV);
+  for (int e0 = chunk * tile; e0 < EV; e0 += chunks * tile) {
+    const int ec = min(tile, EV - e0);  // ec G <= 64, as G = 64 / min(64, EV)
+    if (t < 2 * ec) {
+      const int m = 2 * e0 + t;
+      const ElemConst e = elem_const(M, I, sig, m);
+      consts[t] = DrawConst{e.sq, e.lo, e.hi, nom[m], nom[KU + m]};
     }
+    __syncthreads();
+    for (int p = t; p < cnt * ec; p += 64) {
+      const int r = p / ec, b = p % ec, n = n0 + r;
+      const DrawConst c0 = consts[2 * b], c1 = consts[2 * b + 1];
+      const uint4 x = sample_words(I, n, e0 + b, tick);
+      float4 th;
+      perturb_element(ElemConst{c0.sq, c0.lo, c0.hi, 0}, I.delta, c0.nq, c0.nv, n, x.x, x.y, true, th.x, th.z);
+      perturb_element(ElemConst{c1.sq, c1.lo, c1.hi, 0}, I.delta, c1.nq, c1.nv, n, x.z, x.w, true, th.y, th.w);
+      draws[p] = th;
+    }
+    __syncthreads();
     const int el = t % ec, g = t / ec;
     float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-    const int RT = n_draws / ec;
-    for (int r0 = 0; r0 < cnt; r0 += RT) {
-      const int rt = min(RT, cnt - r0);
-      __syncthreads();  // the constants are there, the last tile has been added
-      for (int p = t; p < rt * ec; p += NT) {
-        const int r = p / ec, b = p % ec, n = n0 + r0 + r;
-        const DrawConst c = consts[b];
-        const uint4 x = sample_words(I, n, e0 + b, tick);
-        float4 th;
-        perturb_element(ElemConst{c.sq[0], c.lo[0], c.hi[0], 0}, I.delta, c.nq[0], c.nv[0], n, x.x, x.y, true, th.x, th.z);
-        perturb_element(ElemConst{c.sq[1], c.lo[1], c.hi[1], 0}, I.delta, c.nq[1], c.nv[1], n, x.z, x.w, true, th.y, th.w);
-        draws[p] = th;
+    if (g < G)
+      for (int r = g; r < cnt; r += G) {
+        const float wr = w[r];
+        const float4 th = draws[r * ec + el];
+        acc.x = fmaf(wr, th.x, acc.x); acc.y = fmaf(wr, th.y, acc.y);
+        acc.z = fmaf(wr, th.z, acc.z); acc.w = fmaf(wr, th.w, acc.w);
       }
-      __syncthreads();
-      if (g < G)
-        for (int r = r0 + (g + G - r0 % G) % G; r < r0 + rt; r += G) {
-          const float wr = w[r];
-          const float4 th = draws[(r - r0) * ec + el];
-          acc.x = fmaf(wr, th.x, acc.x); acc.y = fmaf(wr, th.y, acc.y);
-          acc.z = fmaf(wr, th.z, acc.z); acc.w = fmaf(wr, th.w, acc.w);
-        }
-    }
     __syncthreads();
     if (g < G) draws[g * ec + el] = acc;
     __syncthreads();
@@ -1622,20 +1626,20 @@ __device__ __forceinline__ void regen_weighted_sum_tiles(const DevInst& I, const
         sum.x += a.x; sum.y += a.y; sum.z += a.z; sum.w += a.w;
       }
       const int m = 2 * (e0 + t);
-      mine[m] = sum.x; mine[m + 1] = sum.y;
-      mine[KU + m] = sum.z; mine[KU + m + 1] = sum.w;
+      store_agent(mine + m, sum.x); store_agent(mine + m + 1, sum.y);
+      store_agent(mine + KU + m, sum.z); store_agent(mine + KU + m + 1, sum.w);
     }
-    __syncthreads();  // before the next blocks' constants and draws
+    __syncthreads();  // before the next tile's constants and draws
   }
 }
 
 // Knots of sample n (drawn again, as above) into dst [E].
-template <int NT>
+template <int T>
 __device__ __forceinline__ void regen_sample(const DevInst& I, const float* nom, uint32_t tick, int n, float* dst) {
   const DevModel& M = *I.model;
   const int KU = I.K * I.nu;
   const float* sig = I.sigma + I.iter * I.K;
-  for (int b = threadIdx.x; b < KU / 2; b += NT) {
+  for (int b = threadIdx.x; b < KU / 2; b += T) {
     const uint4 x = sample_words(I, n, b, tick);
     float q0, v0, q1, v1;
     perturb_element(elem_const(M, I, sig, 2 * b), I.delta, nom[2 * b], nom[KU + 2 * b], n, x.x, x.y, true, q0, v0);
@@ -1646,26 +1650,26 @@ __device__ __forceinline__ void regen_sample(const DevInst& I, const float* nom,
   }
 }
 
-// The update of one instance by one workgroup (its part blockIdx.x); o: the
-// call's outputs (null fields: not wanted).
-template <int T, int NT>
-__device__ __forceinline__ void update_body(const DevUpdate& U, const UpdateOut o) {
-  const int part = blockIdx.x, parts = U.parts;
-  if (part >= parts) return;
+// The share of one workgroup in an instance's update: its part, and there the
+// tiles chunk, chunk + chunks, ... of the knot elements; o: the call's outputs (null
+// fields: not wanted).
+template <int T>
+__device__ __forceinline__ void update_body(const DevUpdate& U, const UpdateOut o, int tile) {
+  const int parts = U.parts, chunks = tile && U.regen ? update_chunks(U.E / 4, tile) : 1;
+  if ((int)blockIdx.x >= parts * chunks) return;
+  const int part = blockIdx.x / chunks, chunk = blockIdx.x % chunks;
   const int t = threadIdx.x, N = U.N, E = U.E;
   // the nominal the iteration's samples perturbed (the call's input on its first
   // iteration when the caller's buffer is read in place)
   const float* nom_in = o.nominal_in ? o.nominal_in : U.nominal_in;
   const uint32_t tick = U.regen ? sample_tick(*U.regen) : 0u;  // read before the last part advances it
-  // a tile of draws, or the groups' sums; the wide workgroup's costs in the same space
-  constexpr int kDraws = NT > T ? 1024 : T;
-  __shared__ __align__(16) float4 s_buf[kDraws];
-  __shared__ DrawConst s_const[NT > T ? T : 1];
+  // a tile of draws, or the groups' sums
+  __shared__ __align__(16) float4 s_buf[kUpdTileRows * kUpdTile];
+  static_assert(kUpdTileRows * kUpdTile >= T, "the groups' sums");
+  __shared__ DrawConst s_const[2 * kUpdTile];
   __shared__ float s_w[(65536 + kUpdMaxParts - 1) / kUpdMaxParts];  // this part's normalised weights (N <= 65536)
-  __shared__ float s_tree[T + 1], s_min[NT / 64], s_max[NT / 64];
-  __shared__ int s_arg[NT / 64], s_fin[NT / 64], s_last;
-  float* s_cost = reinterpret_cast<float*>(s_buf);
-  static_assert(NT == T || 4 * kDraws >= 1024, "the wide workgroup stages all costs (N <= 1024)");
+  __shared__ float s_tree[T + 1], s_min[T / 64], s_max[T / 64];
+  __shared__ int s_arg[T / 64], s_fin[T / 64], s_last;
 
   // this part's slice of the samples
   const int slice = (N + parts - 1) / parts;
@@ -1676,23 +1680,19 @@ __device__ __forceinline__ void update_body(const DevUpdate& U, const UpdateOut 
   const float* costs = U.costs;
   float mn = INFINITY, mx = -INFINITY;
   int arg = 0x7fffffff, nf = 0;
-  constexpr int kIn = NT > T ? 4 : 16;
-  for (int m0 = t; m0 < N; m0 += kIn * NT) {
+  constexpr int kIn = 16;
+  for (int m0 = t; m0 < N; m0 += kIn * T) {
     float Sq[kIn];
 #pragma unroll
     for (int q = 0; q < kIn; ++q) {
-      const int n = m0 + q * NT;
+      const int n = m0 + q * T;
       Sq[q] = n < N ? costs[n] : INFINITY;
     }
 #pragma unroll
     for (int q = 0; q < kIn; ++q) {
-      const int n = m0 + q * NT;
+      const int n = m0 + q * T;
       const float S = Sq[q];
-      if constexpr (NT > T) {
-        if (n < N) s_cost[n] = S;
-      } else {
-        if (n >= n0 && n < n0 + cnt) s_w[n - n0] = S;  // the slice's costs
-      }
+      if (n >= n0 && n < n0 + cnt) s_w[n - n0] = S;  // the slice's costs
       if (isfinite(S)) {
         ++nf;
         if (S < mn) { mn = S; arg = n; }
@@ -1713,7 +1713,7 @@ __device__ __forceinline__ void update_body(const DevUpdate& U, const UpdateOut 
   float smin = s_min[0], smax = s_max[0];
   int nstar = s_arg[0], nfin = s_fin[0];
 #pragma unroll
-  for (int k = 1; k < NT / 64; ++k) {
+  for (int k = 1; k < T / 64; ++k) {
     if (s_min[k] < smin || (s_min[k] == smin && s_arg[k] < nstar)) { smin = s_min[k]; nstar = s_arg[k]; }
     smax = fmaxf(smax, s_max[k]);
     nfin += s_fin[k];
@@ -1730,56 +1730,60 @@ __device__ __forceinline__ void update_body(const DevUpdate& U, const UpdateOut 
     return expf(-sh * inv_lam);
   };
   float zs = 0.f;
-  if constexpr (NT > T) {
-    for (int i = t; i < N; i += NT) s_cost[i] = weight(s_cost[i]);
-    __syncthreads();
-    if (t < T)
-      for (int i = t; i < N; i += T) zs += s_cost[i];
-  } else {
-    for (int m0 = t; m0 < N; m0 += kIn * NT) {
-      float Sq[kIn];
+  for (int m0 = t; m0 < N; m0 += kIn * T) {
+    float Sq[kIn];
 #pragma unroll
-      for (int q = 0; q < kIn; ++q) {
-        const int n = m0 + q * NT;
-        Sq[q] = n < N ? costs[n] : INFINITY;
-      }
-#pragma unroll
-      for (int q = 0; q < kIn; ++q) zs += weight(Sq[q]);
+    for (int q = 0; q < kIn; ++q) {
+      const int n = m0 + q * T;
+      Sq[q] = n < N ? costs[n] : INFINITY;
     }
+#pragma unroll
+    for (int q = 0; q < kIn; ++q) zs += weight(Sq[q]);
   }
   const float Z = block_sum<T>(zs, s_tree);
   const float invZ = nfin > 0 ? 1.f / Z : 0.f;
 
   // 3. this part's slice: normalised weights, then its weighted knot sum
-  for (int i = t; i < cnt; i += NT) {
-    const float w = (NT > T ? s_cost[n0 + i] : weight(s_w[i])) * invZ;
+  for (int i = t; i < cnt; i += T) {
+    const float w = weight(s_w[i]) * invZ;
     s_w[i] = w;
-    if (U.weights) U.weights[n0 + i] = w;
+    if (U.weights && chunk == 0) U.weights[n0 + i] = w;
   }
   __syncthreads();
   float* mine = U.partial + (size_t)part * E;
   if (U.regen) {
-    if constexpr (NT > T) regen_weighted_sum_tiles<T, NT>(*U.regen, nom_in, tick, n0, cnt, s_w, s_buf, kDraws, s_const, mine);
-    else regen_weighted_sum<T>(*U.regen, nom_in, tick, n0, cnt, s_w, s_buf, mine);
+    if (T == 64 && tile)
+      regen_weighted_sum_tiles(*U.regen, nom_in, tick, n0, cnt, s_w, s_buf, s_const, mine, tile, chunk, chunks);
+    else
+      regen_weighted_sum<T>(*U.regen, nom_in, tick, n0, cnt, s_w, s_buf, mine);
   } else if ((E & 3) == 0)
-    rows_weighted_sum<4, T, NT>(U.samples + (size_t)n0 * E, cnt, E, s_w, s_buf,
-                            [&](int e, float4 v) { reinterpret_cast<float4*>(mine)[e] = v; });
+    rows_weighted_sum<4, T>(U.samples + (size_t)n0 * E, cnt, E, s_w, s_buf,
+                            [&](int e, float4 v) {
+                              store_agent(mine + 4 * e, v.x); store_agent(mine + 4 * e + 1, v.y);
+                              store_agent(mine + 4 * e + 2, v.z); store_agent(mine + 4 * e + 3, v.w);
+                            });
   else
-    rows_weighted_sum<1, T, NT>(U.samples + (size_t)n0 * E, cnt, E, s_w, s_buf, [&](int e, float v) { mine[e] = v; });
+    rows_weighted_sum<1, T>(U.samples + (size_t)n0 * E, cnt, E, s_w, s_buf, [&](int e, float v) { store_agent(mine + e, v); });
 
   // 4. the last part to finish adds the slices in part order
-  if (parts > 1) {
-    // one fence per workgroup, after all its threads' sums are written: each
-    // device-scope fence writes back the XCD's L2
+  if (parts * chunks > 1) {
+    wait_stores();  // every thread's own, then the workgroup's
     __syncthreads();
     if (t == 0) {
-      __threadfence();
-      s_last = atomicAdd(U.done, 1u) == (uint32_t)(parts - 1);
+      // counted by chunk first (done[1 + chunk], then done[0]): increments of one
+      // address follow each other
+      bool last = true;
+      if (chunks > 1) {
+        last = atomicAdd(U.done + 1 + chunk, 1u) == (uint32_t)(parts - 1);
+        if (last) U.done[1 + chunk] = 0u;  // ready for the next launch
+      }
+      if (last) last = atomicAdd(U.done, 1u) == (uint32_t)((chunks > 1 ? chunks : parts) - 1);
+      s_last = last;
     }
     __syncthreads();
     if (!s_last) return;
     __threadfence();
-    if (t == 0) U.done[0] = 0u;  // ready for the next launch
+    if (t == 0) U.done[0] = 0u;
   }
   __syncthreads();
   float* dst = (U.last_iter && o.knots_out) ? o.knots_out : U.nominal_out;
@@ -1802,11 +1806,11 @@ __device__ __forceinline__ void update_body(const DevUpdate& U, const UpdateOut 
   all_nonfinite += nfin == 0 ? 1 : 0;
   __syncthreads();  // every thread has read the running best
   if (improve) {
-    if (U.regen) regen_sample<NT>(*U.regen, nom_in, tick, nstar, bs);
+    if (U.regen) regen_sample<T>(*U.regen, nom_in, tick, nstar, bs);
     else
-      for (int e = t; e < E; e += NT) bs[e] = U.samples[(size_t)nstar * E + e];
+      for (int e = t; e < E; e += T) bs[e] = U.samples[(size_t)nstar * E + e];
   } else if (first) {
-    for (int e = t; e < E; e += NT) bs[e] = nom_in[e];
+    for (int e = t; e < E; e += T) bs[e] = nom_in[e];
   }
   if (t == 0) {
     bs[E] = S_best;
@@ -1816,17 +1820,17 @@ __device__ __forceinline__ void update_body(const DevUpdate& U, const UpdateOut 
 
   // 6. the nominal: the slices added in part order
   if ((E & 3) == 0)
-    rows_weighted_sum<4, T, NT>(U.partial, parts, E, nullptr, s_buf, [&](int e, float4 v) {
+    rows_weighted_sum<4, T>(U.partial, parts, E, nullptr, s_buf, [&](int e, float4 v) {
       const float c[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
       for (int k = 0; k < 4; ++k) dst[4 * e + k] = nfin > 0 ? c[k] : nom_in[4 * e + k];
     });
   else
-    rows_weighted_sum<1, T, NT>(U.partial, parts, E, nullptr, s_buf, [&](int e, float v) { dst[e] = nfin > 0 ? v : nom_in[e]; });
+    rows_weighted_sum<1, T>(U.partial, parts, E, nullptr, s_buf, [&](int e, float v) { dst[e] = nfin > 0 ? v : nom_in[e]; });
   __syncthreads();
   if (U.last_iter) {
     if (o.best_out)
-      for (int e = t; e < E; e += NT) o.best_out[e] = bs[e];
+      for (int e = t; e < E; e += T) o.best_out[e] = bs[e];
     if (t == 0 && o.info_out) {
       float* inf = reinterpret_cast<float*>(o.info_out);
       int* ii = reinterpret_cast<int*>(o.info_out);
@@ -1837,20 +1841,19 @@ __device__ __forceinline__ void update_body(const DevUpdate& U, const UpdateOut 
   if (U.last_iter && t == 0 && U.tick) U.tick[0] += 1u;
 }
 
-template <int T, int NT>
-__global__ __launch_bounds__(NT) void update_kernel(const DevUpdate* __restrict__ ups,
-                                                    const UpdateOut* __restrict__ outs, UpdateOut single) {
-  update_body<T, NT>(ups[blockIdx.y], outs ? outs[blockIdx.y] : single);
+template <int T>
+__global__ __launch_bounds__(T) void update_kernel(const DevUpdate* __restrict__ ups, const UpdateOut* __restrict__ outs,
+                                                   UpdateOut single, int tile) {
+  update_body<T>(ups[blockIdx.y], outs ? outs[blockIdx.y] : single, tile);
 }
 
 // One instance whose descriptor arrives as a kernel argument (no device copy of
 // it), with no per-call outputs besides the nominal and the weights.
 __global__ __launch_bounds__(kUpdThreads) void update_single_kernel(DevUpdate U) {
-  update_body<kUpdThreads, kUpdThreads>(U, UpdateOut{nullptr, nullptr, nullptr, nullptr});
+  update_body<kUpdThreads>(U, UpdateOut{nullptr, nullptr, nullptr, nullptr}, 0);
 }
-template __global__ void update_kernel<64, 64>(const DevUpdate*, const UpdateOut*, UpdateOut);
-template __global__ void update_kernel<64, 256>(const DevUpdate*, const UpdateOut*, UpdateOut);
-template __global__ void update_kernel<256, 256>(const DevUpdate*, const UpdateOut*, UpdateOut);
+template __global__ void update_kernel<64>(const DevUpdate*, const UpdateOut*, UpdateOut, int);
+template __global__ void update_kernel<kUpdThreads>(const DevUpdate*, const UpdateOut*, UpdateOut, int);
 
 // Warm start (Sec. III-E): the knots of a trajectory shifted forward by n_steps
 // control steps, i.e. its spline at t_k + n_steps dt clamped to the horizon end

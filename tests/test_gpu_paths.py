@@ -233,13 +233,13 @@ def test_mixed_batch_equals_plain_steps(scale):
 
 
 @pytest.mark.parametrize("copies,sizes", [(8, (1, 15, 16, 17, 63, 64, 65, 1008, 1024, 1025)), (2, (1000, 1023, 1025, 4097))])
-@pytest.mark.parametrize("knots", [4, 5])
-def test_update_forms_agree(copies, sizes, knots):
-    """The update's 64-wide sums from workgroups of 256 threads (an instance alone) and
-    of 64 (a launch of more than 1024 parts): sizes around a slice of 16 samples, the
+@pytest.mark.parametrize("name,knots", [("arm", 4), ("arm", 5), ("hexapod", 4)])
+def test_update_forms_agree(copies, sizes, name, knots):
+    """The update's parts spread over workgroups of a few element blocks (an instance
+    alone) and whole (a launch of more than 1024 parts): sizes around a slice of 16 samples, the
     last slice and the width's limit of 1024 samples, an odd and an even number of
-    knot elements (stored samples and samples drawn again)."""
-    m = TREES["arm"]()
+    knot elements (stored samples and samples drawn again), a last tile that is not full."""
+    m = TREES[name]()
     ps = [_params(m, n, horizon=2, knots=knots, iters=2) for n in sizes] * copies
     parts = sum((p["n_samples"] + 15) // 16 for p in ps if p["n_samples"] <= 1024)
     model = mppi.Model(m)
