@@ -1210,7 +1210,9 @@ static hipError_t launch_updates(const DevUpdate* ups, const UpdateOut* outs, co
 }
 // one instance's update (its shape), with the call's outputs o
 static hipError_t launch_update1(const DevUpdate* u, const DevUpdate& h, const UpdateOut& o, hipStream_t s) {
-  // one instance: the narrowest tiles of 256 workgroups at most
+  // one instance: the narrowest tiles of 256 workgroups at most, one to a compute unit
+  // (arm, 2 parts: 13.0 us in one tile of its 12 blocks, 11.8 in three of 4; quadruped,
+  // 4 parts of 48 blocks: 16.1 in tiles of 16, 13.0 of 4, both with a fence)
   int tile = kUpdTile;
   while (tile > 4 && h.parts * update_chunks(h.E / 4, tile / 2) <= 256) tile /= 2;
   if (h.threads == 64)
