@@ -820,6 +820,17 @@ static bool serial_chain(const DevModel& M) {
   return true;
 }
 
+// Whether the depth-specialised body kernels may fold a next lane's inertia into
+// every lane (physics_step): a body one or more levels below the one numbered before
+// it is that one's child, as in a depth-first numbering.  A model only asks that
+// parents come first; other numberings run the kernels of any depth, which fold by
+// the child lists.
+static bool folds_next_lane(const DevModel& M) {
+  for (int b = 1; b < M.nb; ++b)
+    if (M.depth[b] > M.depth[b - 1] && M.parent[b] != b - 1) return false;
+  return true;
+}
+
 // Path kernels: rollouts and LDS bytes of a block (a wavefront).
 static int path_rollouts(const DevModel& M) { return M.path_ok ? 64 / M.path_lanes : 1; }
 static int lane_rollouts(const DevModel& M) { return M.path_ok ? 256 / M.path_lanes : 1; }
@@ -837,12 +848,14 @@ struct Dims {
   int E = 0, nb = 0, nc = 0, nch = 0, natt = 0, ns = 0, depth = 0;
   // every instance added is a legged tree / of four chains of three / a serial chain
   bool leg = true, quad = true, serial = true;
+  bool folds = true;  // folds_next_lane of every instance
   int block_lds = 0;  // bytes of a block of the path kernel (launch_groups)
   void add(const mppi_ctx* c) {
     const DevModel& M = c->m->host;
     leg = leg && legged(M);
     quad = quad && legged_4x3(M);
     serial = serial && serial_chain(M);
+    folds = folds && folds_next_lane(M);
     E = std::max(E, c->E);
     nb = std::max(nb, M.nb);
     nc = std::max(nc, M.nc);
@@ -851,6 +864,8 @@ struct Dims {
     ns = std::max(ns, M.team_slots);
     depth = std::max(depth, M.max_depth);
   }
+  // levels that a body kernel has to be specialised for (beyond 6: any depth)
+  int body_depth() const { return folds ? depth : kMaxBodies; }
 };
 static Dims dims_of(const mppi_ctx* c) {
   Dims d;
@@ -1024,11 +1039,11 @@ static std::vector<LaunchGroup> launch_groups(const std::vector<const mppi_ctx*>
 }
 
 // the body schedule's kernel for trees at most 3 or 6 levels deep has its level
-// loops unrolled; deeper trees take the general one
+// loops unrolled; deeper trees, and numberings it does not fold, take the general one
 template <int G>
 static hipError_t launch_rollout_G(int blocks, const DevInst* insts, const int2* work, const LaunchShape& sh,
                                    const Dims& dm, hipStream_t s, const float* x0_in, const float* nominal_in) {
-  const int depth = dm.depth;
+  const int depth = dm.body_depth();
   if constexpr (G == 16) {
     if (depth <= 3 && dm.quad) {
       hipLaunchKernelGGL((rollout_kernel<16, 3, 2>), dim3(blocks), dim3(64), sh.lds, s, insts, work, sh.stride,
@@ -1126,15 +1141,16 @@ static hipError_t launch_persistent_k(Kern kern, int n_items, const LaunchShape&
 template <int G>
 static hipError_t launch_persistent_body(int n_items, const LaunchShape& sh, const Dims& dm, unsigned int* counter,
                                          hipStream_t s, const DevInst* insts, const int2* work) {
+  const int depth = dm.body_depth();
 #define P_ARGS n_items, sh, counter, s, insts, work, n_items, counter, sh.stride, sh.table
   if constexpr (G == 16)
-    if (dm.depth <= 3 && dm.quad) return launch_persistent_k(rollout_persistent_kernel<16, 3, 2>, P_ARGS);
+    if (depth <= 3 && dm.quad) return launch_persistent_k(rollout_persistent_kernel<16, 3, 2>, P_ARGS);
   if constexpr (G >= 8 && G <= 32)
-    if (dm.depth <= 3 && dm.leg) return launch_persistent_k(rollout_persistent_kernel<G, 3, 1>, P_ARGS);
+    if (depth <= 3 && dm.leg) return launch_persistent_k(rollout_persistent_kernel<G, 3, 1>, P_ARGS);
   if constexpr (G == 4 || G == 8)
-    if (dm.depth <= 3 && dm.serial) return launch_persistent_k(rollout_persistent_kernel<G, 3, 3>, P_ARGS);
-  if (dm.depth <= 3) return launch_persistent_k(rollout_persistent_kernel<G, 3, 0>, P_ARGS);
-  if (dm.depth <= 6) return launch_persistent_k(rollout_persistent_kernel<G, 6, 0>, P_ARGS);
+    if (depth <= 3 && dm.serial) return launch_persistent_k(rollout_persistent_kernel<G, 3, 3>, P_ARGS);
+  if (depth <= 3) return launch_persistent_k(rollout_persistent_kernel<G, 3, 0>, P_ARGS);
+  if (depth <= 6) return launch_persistent_k(rollout_persistent_kernel<G, 6, 0>, P_ARGS);
   return launch_persistent_k(rollout_persistent_kernel<G, 0, 0>, P_ARGS);
 #undef P_ARGS
 }
@@ -1876,7 +1892,7 @@ extern "C" mppi_status mppi_debug_rollouts(mppi_ctx* c, const float* d_state, co
 template <int G>
 static hipError_t launch_trace_G(const DevInst* inst, int N, const LaunchShape& sh, const Dims& dm, hipStream_t s) {
   const int blocks = (N + sh.groups - 1) / sh.groups;
-  const int depth = dm.depth;
+  const int depth = dm.body_depth();
   if constexpr (G == 16) {
     if (depth <= 3 && dm.quad) {
       hipLaunchKernelGGL((rollout_trace_kernel<16, 3, 2>), dim3(blocks), dim3(64), sh.lds, s, inst, nullptr,
