@@ -297,9 +297,18 @@ static void build_path_tables(DevModel& M) {
       M.path_src[p][i] = 0xffffffffu;
     }
   if (nb <= fb) return;
-  // one path per leaf, leaves in body order
+  // one path per leaf, in the order of a depth-first walk that takes the children of
+  // a body by their numbers, however the tree is numbered: so the first paths that
+  // hold a body's children increase with the children, and sums over paths are the
+  // body schedule's sums over children
   int np = 0, len = 0;
-  for (int b = fb; b < nb; ++b) {
+  std::vector<int> walk;  // bodies to visit, the next one last
+  for (int b = nb - 1; b >= fb; --b)
+    if (M.parent[b] == (fb ? 0 : -1)) walk.push_back(b);
+  while (!walk.empty()) {
+    const int b = walk.back();
+    walk.pop_back();
+    for (int k = M.n_child[b] - 1; k >= 0; --k) walk.push_back(M.child[b][k]);
     if (M.n_child[b] > 0) continue;
     if (np >= kMaxPaths) return;
     std::vector<int> up;
@@ -337,7 +346,7 @@ static void build_path_tables(DevModel& M) {
       }
     }
   if (fb) {
-    // the base's children in body order are brought by increasing paths
+    // the base's children, by their numbers, are brought by increasing paths
     for (int k = 0; k < M.n_child[0]; ++k) M.path_base_mask |= 1 << first[M.child[0][k]];
   }
   for (int i = 0; i < kMaxPath; ++i)

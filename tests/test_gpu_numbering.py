@@ -152,3 +152,38 @@ def test_traced_states_match_oracle():
         err = np.abs(got[h] - ref).max() / scale
         print(f"step {h}: {err:.2e} (oracle-f32 {f32:.2e})")
         assert err <= max(1e-3, 4 * f32), h
+
+
+@pytest.mark.parametrize("form", ["quad", "lane"])
+@pytest.mark.parametrize("name", sorted(PARENTS))
+def test_path_kernel_adds_children_in_body_order(name, form):
+    """The default lane count (the path kernel) against another one, bit for bit: the
+    paths that bring the base's children are added in the children's order."""
+    m = _model(name)
+    # the one-lane form's range begins past the quad form's wavefronts of one turn of the device
+    n = 67 if form == "quad" else 64 * torch.cuda.get_device_properties(0).multi_processor_count + 5
+    p = _params(m, n, 40 if form == "quad" else 20)
+    model = mppi.Model(m)
+    c = mppi.Controller(model, p, 77)
+    a, b = _step(c, m, p), _step(mppi.Controller(model, p, 77, lanes=2 * c.lanes), m, p)
+    assert np.all(np.isfinite(a["costs"]))
+    for k in a:
+        assert np.array_equal(a[k], b[k]), (name, k, int(np.sum(a[k] != b[k])))
+
+
+@pytest.mark.parametrize("name", sorted(PARENTS))
+def test_prediction_equals_the_traced_rollout(name):
+    m = _model(name)
+    p = _params(m, 3, 12)
+    c = mppi.Controller(mppi.Model(m), p, 5)
+    kn, x = _dev(synth.nominal_knots(m, p["n_knots"])), _dev(m["x0"])
+    nx, rec = m["n_q"] + m["n_v"], m["n_q"] + 2 * m["n_v"] + 2
+    trace = torch.zeros((1, 13, rec), device="cuda")
+    c.trace(x, kn, 0, 0, torch.tensor([0, -1, -1], dtype=torch.int32, device="cuda"), trace,
+            torch.zeros((3, c.E), device="cuda"), torch.zeros(3, device="cuda"),
+            torch.zeros((3, 12), dtype=torch.int32, device="cuda"))
+    for n in (1, 7, 12):
+        out = torch.zeros(nx, device="cuda")
+        c.predict(x, kn, n, out)
+        torch.cuda.synchronize()
+        assert np.array_equal(out.cpu().numpy(), trace[0, n, :nx].cpu().numpy()), n
