@@ -11,14 +11,21 @@ scratch memory (register spills), and the body-schedule rollout kernel and every
 persistent kernel must fit two wavefronts per SIMD (at most 256 VGPRs), which
 launches of more than one wavefront per SIMD rely on (the persistent forms size
 their grids to the occupancy they get).  The path kernel holds one wavefront per SIMD
-with all 512 registers and launches for that.
+with all 512 registers and launches for that.  The machine code is checked for the
+wait states that assembly blocks have to keep (hazards.py).
 """
 import os
 import re
 import subprocess
+import sys
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
+if ROOT not in sys.path:
+    sys.path.insert(0, ROOT)
+
+from paper_2511_19204_amd import hazards  # noqa: E402
+
 SOURCES = [os.path.join(HERE, "csrc", f) for f in ("mppi_kernels.hip", "mppi_paths.hip", "mppi_api.hip")]
 HEADERS = [os.path.join(HERE, "csrc", f) for f in ("mppi_dev.hpp", "mppi_step.hpp", "mppi_path.hpp", "mppi_lane.hpp")]
 HEADERS.append(os.path.join(ROOT, "include", "mppi.h"))
@@ -111,6 +118,8 @@ def build(force: bool = True, verbose: bool = False, sanitize: bool = False) -> 
     if verbose and msgs:
         print("\n".join(msgs))
     check_resources(resource_usage("\n".join(outs)))
+    if not sanitize:  # (the same device code)
+        hazards.check(tmp)
     os.replace(tmp, lib)
     return lib
 

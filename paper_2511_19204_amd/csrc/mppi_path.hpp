@@ -62,8 +62,9 @@ __device__ __forceinline__ float cross_k(float a, float b) { return cross_k(rot1
 // kernel's.  The values are those of the plain expressions in the comments.
 // A DPP operand must not have been written by the two instructions before it:
 // every block first issues instructions without DPP operands on its inputs (or
-// an s_nop), and inside a block a value is read through DPP at the earliest
-// three instructions after it was written.
+// an s_nop), since a register copy may stand in front of it, and inside a block a
+// value is read through DPP at the earliest three instructions after it was
+// written.  The build checks the machine code.
 #define Q0 " quad_perm:[0,0,0,0]\n"
 #define Q1 " quad_perm:[1,1,1,1]\n"
 #define Q2 " quad_perm:[2,2,2,2]\n"
@@ -406,28 +407,31 @@ __device__ __forceinline__ void path_backward(const PathInertia& I, const PathFr
   const float Dv = (arm + gain) + d;
   J.invD = rcp(Dv);
   J.u = tau - s;
-  const float Wa = J.Ua * J.invD, Wl = J.Ul * J.invD;
+  const float Wl = J.Ul * J.invD;
+  // uD = u / D and Wa = Ua / D (plain reads, before those through DPP), then
   // Ia = IA - U W^T (entry (r, c) with r <= c takes U_r W_c), then y = Ia c
   PathInertia X = I;
-  float ya, yl, t0, t1;
-  asm(FMAC "%6, -%16, %19" Q0 FMAC "%7, -%16, %19" Q1 FMAC "%8, -%16, %19" Q2   // T_j -= Ua_j Wl
-      FMAC "%0, -%16, %18" Q0                                                   // A_0 -= Ua_0 Wa
-      FMAC "%3, -%19, %16" Q0 FMAC "%4, -%19, %16" Q1 FMAC "%5, -%19, %16" Q2   // B_j -= Ua Wl_j
-      MOV "%14, %18" HI1 MOV "%15, %19" HI1
-      FMAC "%2, -%18, %16" Q2                                                   // A_2 -= Ua Wa_2
-      FMAC "%1, -%16, %14" LO1
-      FMAC "%9, -%17, %19" Q0 FMAC "%11, -%19, %17" Q2 FMAC "%10, -%17, %15" LO1  // C
-      MUL "%12, %20, %0" Q0 MUL "%13, %20, %6" Q0
-      FMAC "%12, %20, %1" Q1 FMAC "%13, %20, %7" Q1
-      FMAC "%12, %20, %2" Q2 FMAC "%13, %20, %8" Q2
-      FMAC "%12, %21, %3" Q0 FMAC "%13, %21, %9" Q0
-      FMAC "%12, %21, %4" Q1 FMAC "%13, %21, %10" Q1
-      FMAC "%12, %21, %5" Q2 FMAC "%13, %21, %11" Q2
+  float ya, yl, t0, t1, uD, Wa;
+  asm("v_mul_f32 %16, %23, %24\n"
+      "v_mul_f32 %17, %18, %24\n"
+      FMAC "%6, -%18, %20" Q0 FMAC "%7, -%18, %20" Q1 FMAC "%8, -%18, %20" Q2   // T_j -= Ua_j Wl
+      FMAC "%0, -%18, %17" Q0                                                   // A_0 -= Ua_0 Wa
+      FMAC "%3, -%20, %18" Q0 FMAC "%4, -%20, %18" Q1 FMAC "%5, -%20, %18" Q2   // B_j -= Ua Wl_j
+      MOV "%14, %17" HI1 MOV "%15, %20" HI1
+      FMAC "%2, -%17, %18" Q2                                                   // A_2 -= Ua Wa_2
+      FMAC "%1, -%18, %14" LO1
+      FMAC "%9, -%19, %20" Q0 FMAC "%11, -%20, %19" Q2 FMAC "%10, -%19, %15" LO1  // C
+      MUL "%12, %21, %0" Q0 MUL "%13, %21, %6" Q0
+      FMAC "%12, %21, %1" Q1 FMAC "%13, %21, %7" Q1
+      FMAC "%12, %21, %2" Q2 FMAC "%13, %21, %8" Q2
+      FMAC "%12, %22, %3" Q0 FMAC "%13, %22, %9" Q0
+      FMAC "%12, %22, %4" Q1 FMAC "%13, %22, %10" Q1
+      FMAC "%12, %22, %5" Q2 FMAC "%13, %22, %11" Q2
       : "+v"(X.A[0]), "+v"(X.A[1]), "+v"(X.A[2]), "+v"(X.B[0]), "+v"(X.B[1]), "+v"(X.B[2]), "+v"(X.T[0]), "+v"(X.T[1]),
-        "+v"(X.T[2]), "+v"(X.C[0]), "+v"(X.C[1]), "+v"(X.C[2]), "=&v"(ya), "=&v"(yl), "=&v"(t0), "=&v"(t1)
-      : "v"(J.Ua), "v"(J.Ul), "v"(Wa), "v"(Wl), "v"(F.ca), "v"(F.cl));
+        "+v"(X.T[2]), "+v"(X.C[0]), "+v"(X.C[1]), "+v"(X.C[2]), "=&v"(ya), "=&v"(yl), "=&v"(t0), "=&v"(t1), "=&v"(uD),
+        "=&v"(Wa)
+      : "v"(J.Ua), "v"(J.Ul), "v"(Wl), "v"(F.ca), "v"(F.cl), "v"(J.u), "v"(J.invD));
   // pa = pA + Ia c + U u / D
-  const float uD = J.u * J.invD;
   const float pa = I.pa + ya + J.Ua * uD;
   const float pl = I.pl + yl + J.Ul * uD;
   // carried to the parent's origin: C' = C, B' = B + E C, A' = A - B'E - (B E)^T
