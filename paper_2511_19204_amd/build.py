@@ -27,7 +27,7 @@ if ROOT not in sys.path:
 from paper_2511_19204_amd import hazards  # noqa: E402
 
 SOURCES = [os.path.join(HERE, "csrc", f) for f in ("mppi_kernels.hip", "mppi_paths.hip", "mppi_api.hip")]
-HEADERS = [os.path.join(HERE, "csrc", f) for f in ("mppi_dev.hpp", "mppi_step.hpp", "mppi_path.hpp", "mppi_lane.hpp")]
+HEADERS = [os.path.join(HERE, "csrc", f) for f in ("mppi_dev.hpp", "mppi_step.hpp", "mppi_path.hpp", "mppi_lane.hpp", "mppi_forms.hpp")]
 HEADERS.append(os.path.join(ROOT, "include", "mppi.h"))
 LIB = os.path.join(HERE, "libmppi.so")
 LIB_SAN = os.path.join(HERE, "libmppi_san.so")

@@ -26,6 +26,7 @@
 
 #include "../../include/mppi.h"
 #include "mppi_dev.hpp"
+#include "mppi_forms.hpp"
 
 namespace mppi {
 // kernels (mppi_kernels.hip)
@@ -118,6 +119,7 @@ struct mppi_ctx {
   // state prediction: measured state, trajectory knots, a cost slot, its descriptor
   float *x_meas = nullptr, *pred_knots = nullptr, *pred_cost = nullptr;
   DevInst* d_pred_inst = nullptr;
+  FormDesc form;  // for the choice of a launch's kernels (form_desc)
   uint32_t* tick = nullptr;
   float* upd_partial = nullptr;  // [update_shape(N).parts][E] update scratch
   uint32_t* upd_done = nullptr;  // [1 + kUpdMaxChunks] update workgroups finished (0 between launches)
@@ -609,6 +611,7 @@ static void build_tables(mppi_ctx* c) {
   }
 }
 
+static FormDesc form_desc(const mppi_ctx* c);
 extern "C" mppi_status mppi_create(const mppi_model* m, const mppi_params* p, uint64_t seed, mppi_ctx** out) {
   if (!m || !p || !out) return fail(MPPI_EINVAL, "null argument");
   if (p->n_samples < 1 || p->n_samples > 65536) return fail(MPPI_EINVAL, "n_samples must be in 1..65536");
@@ -710,6 +713,7 @@ extern "C" mppi_status mppi_create(const mppi_model* m, const mppi_params* p, ui
   }
   if ((e = hipMemcpy(c->d_insts, c->h_insts.data(), c->I * sizeof(DevInst), hipMemcpyHostToDevice)) != hipSuccess) return bail(e, "upload insts");
   if ((e = hipMemcpy(c->d_ups, c->h_ups.data(), c->I * sizeof(DevUpdate), hipMemcpyHostToDevice)) != hipSuccess) return bail(e, "upload ups");
+  c->form = form_desc(c);
   *out = c;
   return MPPI_OK;
 }
@@ -848,7 +852,8 @@ static int path_len_of_kernel(const DevModel& M) { return M.path_len <= 3 ? 3 : 
 static int path_block_bytes(const DevModel& M, int E) {
   return (path_table_floats(M.nc, M.n_paths, path_len_of_kernel(M)) + path_rollouts(M) * path_group_floats(E)) *
          (int)sizeof(float);
-}static int lane_block_bytes(const DevModel& M, int E) {
+}
+static int lane_block_bytes(const DevModel& M, int E) {
   return (lane_table_floats(M.nc, M.n_paths, path_len_of_kernel(M)) + lane_rollouts(M) * path_group_floats(E)) *
          (int)sizeof(float);
 }
@@ -922,87 +927,55 @@ static int rollouts_per_block(int key, const Dims& dm, const mppi_ctx* c) {
 
 // Whether the path kernels take an instance: its tree fits them, its knots fit a
 // block's LDS, and its end-effector cost (if it has one) is a path body's.
-constexpr int kPathLds = 64 * 1024;
-constexpr int kCuLds = 160 * 1024;  // of a compute unit
 static bool path_fits(const mppi_ctx* c) {
   const DevModel& M = c->m->host;
   if (!M.path_ok || (M.fb && c->p.cost_kind == 0 && M.ee_body == 0)) return false;
   return path_block_bytes(M, c->E) <= kPathLds;
 }
 
+// What the choice of a form looks at, for an instance at its default lane count.
+static FormDesc form_desc(const mppi_ctx* c) {
+  const DevModel& M = c->m->host;
+  const Dims dm = dims_of(c);
+  FormDesc d;
+  d.path = path_fits(c);
+  if (!d.path) return d;
+  d.folds = dm.folds;
+  d.floating = M.fb;
+  d.serial = dm.serial;
+  d.shared = M.path_branch != 0;
+  d.depth = M.max_depth;
+  d.path_len = path_len_of_kernel(M);
+  d.path_lanes = M.path_lanes;
+  d.body_key = next_pow2(M.nb);
+  d.base_children = M.fb ? M.n_child[0] : 0;
+  for (int b = 0; b < M.nb; ++b) d.contacts_max = std::max(d.contacts_max, M.c_count[b]);
+  for (int i = 0; i < kMaxPath; ++i) d.contacts_path += M.path_cmax[i];
+  d.samples = c->N;
+  d.steps = (double)c->H * M.nsub;
+  d.quad_lds = path_block_bytes(M, c->E);
+  d.lane_lds = lane_block_bytes(M, c->E);
+  d.body_lds = launch_shape(d.body_key, dm).lds;
+  return d;
+}
+
 // The keys the instances of one launch run with: kPathKey or kLaneKey (the path
 // kernel's two forms, which may share a launch) for the body schedule at its
-// default lane count where the tree fits them, else the chosen schedule.
-//
-// A SIMD holds one wavefront of either form.  The quad form's step is the
-// shorter (the one-lane form's takes 1.4 to 1.9 times as long: 3.4 and 5.4 us for
-// the quadruped, 7.4 and 12.2 for the humanoid, 2.0 and 3.4 for the arm), the
-// one-lane form needs a quarter of the wavefronts.  So while all quad-form
-// wavefronts are resident at once they are taken (quadruped, 4 096 samples x 60
-// steps: 0.25 ms, one-lane form 0.35, one lane per body 0.28); past that a second
-// turn of the SIMDs costs more than the longer step (6 144 samples: 0.44 / 0.37 /
-// 0.41; 16 384: 0.84 / 0.39 / 0.76; hexapod at 4 096: 0.50 / 0.38 / 0.44; humanoid
-// at 16 384: 1.73 / 0.81 / 2.55).  In a mixed launch that does not fit at once the
-// longest rollouts keep the quad form as far as that shortens the launch.
-constexpr double kLaneStep = 1.65;  // one-lane step over quad step
-// The quad form's time per rollout of an instance (microseconds: 0.65 a body of
-// the path, 1.3 the floating base, 0.4 a contact point).
-static double quad_time(const mppi_ctx* c) {
-  const DevModel& M = c->m->host;
-  double t = 0.65 * path_len_of_kernel(M) + 1.3 * M.fb;
-  for (int i = 0; i < kMaxPath; ++i) t += 0.4 * M.path_cmax[i];
-  return t * c->H * M.nsub;
+// default lane count where choose_forms says so, else the chosen schedule.
+static bool may_take_path(const mppi_ctx* c) { return c->form.path && c->lanes == c->form.body_key; }
+static int key_of_form(const mppi_ctx* c, Form f) {
+  return f == kFormQuad ? kPathKey : f == kFormLane ? kLaneKey : c->lanes;
+}
+static int choose_key(const mppi_ctx* c) {
+  return may_take_path(c) ? key_of_form(c, choose_form(c->form, c->m->simds)) : c->lanes;
 }
 static std::vector<int> choose_keys(const std::vector<const mppi_ctx*>& list) {
   std::vector<int> keys(list.size());
-  struct Cand {
-    int i;
-    double quad, quad_waves, lane_waves;  // time of a rollout in the quad form, wavefronts
-    int lane_lds;
-  };
-  std::vector<Cand> cand;
-  double waves = 0;
-  for (int i = 0; i < (int)list.size(); ++i) {
-    const mppi_ctx* c = list[i];
-    const DevModel& M = c->m->host;
-    keys[i] = c->lanes;
-    if (c->lanes != next_pow2(M.nb) || !path_fits(c)) continue;
-    keys[i] = kPathKey;
-    const int rp = path_rollouts(M), rl = lane_rollouts(M);
-    cand.push_back({i, quad_time(c), (double)((c->N + rp - 1) / rp), (double)((c->N + rl - 1) / rl),
-                    lane_block_bytes(M, c->E)});
-    waves += cand.back().quad_waves;
-  }
-  if (cand.empty() || waves <= list[cand[0].i]->m->simds) return keys;
-  const double simds = list[cand[0].i]->m->simds;
-  // the first k of the candidates, longest first, in the quad form, the rest in
-  // the one-lane form: the launch lasts about as long as its longest rollout or
-  // its work spread over the SIMDs, whichever is more (one instance: whole turns)
-  std::stable_sort(cand.begin(), cand.end(), [](const Cand& a, const Cand& b) { return a.quad > b.quad; });
-  const int n = (int)cand.size();
-  // the one-lane form keeps 64 / G rollouts' knots in a block's LDS: a mixed launch
-  // takes it where four blocks fit a compute unit, one instance also with fewer
-  auto lane_ok = [&](const Cand& c) { return c.lane_lds <= (n == 1 ? kPathLds : kCuLds / 4); };
-  const double lane_simds = n == 1 ? simds / 4 * std::min(4, kCuLds / cand[0].lane_lds) : simds;
-  int best_k = n;
-  double best = 1e300;
-  for (int k = n; k >= 0; --k) {
-    double longest = 0, work = 0;
-    for (int j = 0; j < n; ++j) {
-      const Cand& c = cand[j];
-      const bool lane = j >= k && lane_ok(c);
-      const double t = lane ? kLaneStep * c.quad : c.quad, w = lane ? c.lane_waves : c.quad_waves;
-      longest = std::max(longest, t);
-      work += t * (n == 1 ? std::ceil(w / (lane ? lane_simds : simds)) * simds : w);
-    }
-    const double est = n == 1 ? work / simds : std::max(longest, work / simds) + 0.2 * std::min(longest, work / simds);
-    if (est < best) {
-      best = est;
-      best_k = k;
-    }
-  }
-  for (int j = best_k; j < n; ++j)
-    if (lane_ok(cand[j])) keys[cand[j].i] = kLaneKey;
+  std::vector<FormDesc> desc(list.size());
+  for (size_t i = 0; i < list.size(); ++i)
+    if (may_take_path(list[i])) desc[i] = list[i]->form;
+  const std::vector<Form> form = choose_forms(desc, list.empty() ? 0 : list[0]->m->simds);
+  for (size_t i = 0; i < list.size(); ++i) keys[i] = key_of_form(list[i], form[i]);
   return keys;
 }
 // The launches of a list of instances: per launch the key (kPathKey for both
@@ -1034,7 +1007,7 @@ static std::vector<LaunchGroup> launch_groups(const std::vector<const mppi_ctx*>
     auto length = [&](int a) {
       const DevModel& M = list[a]->m->host;
       if (g.key != kPathKey) return (double)list[a]->H * M.nsub * M.nb;
-      return quad_time(list[a]) * (keys[a] == kLaneKey ? kLaneStep : 1.0);
+      return quad_weight(list[a]->form) * (keys[a] == kLaneKey ? kLaneWeight : 1.0);
     };
     std::stable_sort(kv.second.begin(), kv.second.end(), [&](int x, int y) { return length(x) > length(y); });
     for (int a : kv.second) {
@@ -1262,7 +1235,7 @@ static mppi_status run_iterations(mppi_ctx* c, float* d_knots_out, float* d_best
                                   float* d_costs, hipStream_t s, const float* x0_in = nullptr,
                                   const float* nominal_in = nullptr) {
   Dims dm = dims_of(c);
-  const int key = choose_keys({c})[0];
+  const int key = choose_key(c);
   dm.block_lds = key == kLaneKey ? lane_block_bytes(c->m->host, c->E) : path_block_bytes(c->m->host, c->E);
   const int R = rollouts_per_block(key, dm, c);
   const int blocks = (c->N + R - 1) / R;
