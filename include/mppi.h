@@ -408,6 +408,12 @@ mppi_status mppi_debug_trace(mppi_ctx* c, const float* d_state, const float* d_k
 mppi_status mppi_debug_update(mppi_ctx* c, const float* d_costs, const float* d_samples,
                               const float* d_knots_in, float* d_knots_out, float* d_weights, void* stream);
 
+/* Kernel form of each instance's rollouts in a launch of these n instances (one:
+ * mppi_step; more: a batch or a graph without the persistent form): forms [n]
+ * host = 0 the chosen schedule's own kernel, 1 a quad of lanes per root-to-leaf
+ * path, 2 one lane per path (see mppi_schedule).  Launches nothing. */
+mppi_status mppi_debug_launch_forms(int32_t n, mppi_ctx* const* ctxs, int32_t* forms);
+
 /* ---- Without allocation -------------------------------------------------- */
 
 /* For callers that cannot allocate device memory -- code under HIP graph

@@ -1944,6 +1944,15 @@ extern "C" mppi_status mppi_debug_trace(mppi_ctx* c, const float* d_state, const
   return MPPI_OK;
 }
 
+extern "C" mppi_status mppi_debug_launch_forms(int32_t n, mppi_ctx* const* ctxs, int32_t* forms) {
+  if (n < 1 || !ctxs || !forms) return fail(MPPI_EINVAL, "null argument");
+  for (int i = 0; i < n; ++i)
+    if (!ctxs[i]) return fail(MPPI_EINVAL, "null argument");
+  const std::vector<int> keys = choose_keys(std::vector<const mppi_ctx*>(ctxs, ctxs + n));
+  for (int i = 0; i < n; ++i) forms[i] = keys[i] == kPathKey ? kFormQuad : keys[i] == kLaneKey ? kFormLane : kFormBody;
+  return MPPI_OK;
+}
+
 extern "C" mppi_status mppi_debug_update(mppi_ctx* c, const float* d_costs, const float* d_samples,
                                          const float* d_knots_in, float* d_knots_out, float* d_weights, void* stream) {
   if (!c || !d_costs || !d_samples || !d_knots_in || !d_knots_out) return fail(MPPI_EINVAL, "null argument");

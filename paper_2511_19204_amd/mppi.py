@@ -72,7 +72,7 @@ EXPORTS = [
     "mppi_get_tick", "mppi_set_schedule", "mppi_get_schedule", "mppi_set_lanes_per_rollout",
     "mppi_get_lanes_per_rollout", "mppi_set_targets", "mppi_step", "mppi_predict", "mppi_shift_knots", "mppi_tick",
     "mppi_step_batch", "mppi_debug_philox", "mppi_debug_samples", "mppi_debug_dynamics",
-    "mppi_debug_rollouts", "mppi_debug_trace", "mppi_debug_update", "mppi_profile_enable", "mppi_profile_read",
+    "mppi_debug_rollouts", "mppi_debug_trace", "mppi_debug_update", "mppi_debug_launch_forms", "mppi_profile_enable", "mppi_profile_read",
     "mppi_set_batch_options", "mppi_graph_create", "mppi_graph_launch", "mppi_graph_destroy",
     "mppi_autotune", "mppi_server_create", "mppi_server_submit", "mppi_server_submit_tick", "mppi_server_poll",
     "mppi_server_drain", "mppi_server_stats", "mppi_server_destroy", "mppi_update_noalloc",
@@ -118,6 +118,7 @@ def lib():
         L.mppi_debug_rollouts.argtypes = [vp, vp, vp, vp, vp, vp]
         L.mppi_debug_trace.argtypes = [vp, vp, vp, i32, u32, vp, vp, vp, vp, vp, vp]
         L.mppi_debug_update.argtypes = [vp, vp, vp, vp, vp, vp, vp]
+        L.mppi_debug_launch_forms.argtypes = [i32, vp, C.POINTER(i32)]
         L.mppi_profile_enable.argtypes = [vp, i32]
         L.mppi_profile_read.argtypes = [vp, C.POINTER(C.c_double), C.POINTER(i32),
                                         C.POINTER(C.c_double), C.POINTER(i32)]
@@ -428,6 +429,14 @@ def _ptr_array(xs):
     n = len(xs)
     return (C.c_void_p * n)(*[(x.h if isinstance(x, Controller) else _addr(x)) if x is not None else None
                               for x in xs])
+
+
+def launch_forms(ctrls):
+    """Kernel form of each controller in a launch of them: "schedule" (the chosen
+    schedule's own kernel), "quad" or "lane" per root-to-leaf path."""
+    out = (C.c_int32 * len(ctrls))()
+    _check(lib().mppi_debug_launch_forms(len(ctrls), _ptr_array(ctrls), out), "mppi_debug_launch_forms")
+    return [("schedule", "quad", "lane")[f] for f in out]
 
 
 def set_batch_options(persistent):

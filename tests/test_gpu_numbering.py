@@ -27,6 +27,7 @@ PARENTS = {
     "four_ragged": [-1, 0, 0, 0, 0, 1, 3, 4, 6],
     # eight legs of one to three bodies, level by level
     "eight_ragged": [-1, 0, 0, 0, 0, 0, 0, 0, 0, 8, 1, 6, 3, 10, 9],
+    "six_of_four": [-1] + [0] * 6 + list(range(1, 19)),
     # the bodies several paths share are numbered before and after other legs
     "forked": [-1, 0, 0, 2, 1, 3, 1, 2, 6, 4, 5],
     "forked_fixed": [-1, -1, 0, 1, 0, 1, 3, 2, 4],
