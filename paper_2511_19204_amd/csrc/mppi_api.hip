@@ -1017,6 +1017,11 @@ static std::vector<LaunchGroup> launch_groups(const std::vector<const mppi_ctx*>
     }
     out.push_back(std::move(g));
   }
+  // Persistent kernels of the widest rollouts first: a launch of fewer wavefronts than
+  // SIMDs right behind the updates' workgroups is placed two to a SIMD here and there
+  // (27 arms' 834 wavefronts: 495 to 750 us by turns, 500 behind another rollout
+  // kernel; 64 robots' persistent round 15.4 -> 15.1 ms).
+  if (persistent) std::reverse(out.begin(), out.end());
   return out;
 }
 
