@@ -16,8 +16,10 @@ wait states that assembly blocks have to keep (hazards.py).
 """
 import os
 import re
+import shutil
 import subprocess
 import sys
+import tempfile
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
@@ -93,34 +95,34 @@ def build(force: bool = True, verbose: bool = False, sanitize: bool = False) -> 
         mt = os.path.getmtime(lib)
         if all(os.path.getmtime(f) <= mt for f in SOURCES + HEADERS):
             return lib
-    tmp = lib + ".tmp"
     extra = SAN_HOST if sanitize else []
     flags = [f for f in FLAGS if f != "-shared"] + [f for f in extra if f != "-shared-libsan"]
-    # the sources side by side (minutes each), then linked
-    objs = [f"{tmp}.{os.path.splitext(os.path.basename(src))[0]}.o" for src in SOURCES]
-    procs = [subprocess.Popen(["hipcc", *flags, "-Rpass-analysis=kernel-resource-usage", "-c", src, "-o", obj],
-                              stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
-             for src, obj in zip(SOURCES, objs)]
-    outs = [p.communicate()[0] for p in procs]
-    rc = [p.returncode for p in procs]
-    if not any(rc):
-        res = subprocess.run(["hipcc", *FLAGS, *extra, *objs, "-o", tmp], capture_output=True, text=True)
-        outs.append(res.stdout + res.stderr)
-        rc.append(res.returncode)
-    for obj in objs:
-        if os.path.exists(obj):
-            os.remove(obj)
-    noise = ("packed-fp32-ops", "kernel-resource-usage")
-    msgs = [ln for ln in "\n".join(outs).splitlines()
-            if not any(n in ln for n in noise) and ln.strip() and not ln.startswith(" ") and ln.strip() != "^"]
-    if any(rc):
-        raise RuntimeError("hipcc failed:\n" + "\n".join(msgs))
-    if verbose and msgs:
-        print("\n".join(msgs))
-    check_resources(resource_usage("\n".join(outs)))
-    if not sanitize:  # (the same device code)
-        hazards.check(tmp)
-    os.replace(tmp, lib)
+    # objects, and what the compiler leaves beside them, stay out of the tree
+    with tempfile.TemporaryDirectory(prefix="mppi_build_") as d:
+        built = os.path.join(d, "libmppi.so")
+        # the sources side by side (minutes each), then linked
+        objs = [os.path.join(d, os.path.splitext(os.path.basename(src))[0] + ".o") for src in SOURCES]
+        procs = [subprocess.Popen(["hipcc", *flags, "-Rpass-analysis=kernel-resource-usage", "-c", src, "-o", obj],
+                                  stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+                 for src, obj in zip(SOURCES, objs)]
+        outs = [p.communicate()[0] for p in procs]
+        rc = [p.returncode for p in procs]
+        if not any(rc):
+            res = subprocess.run(["hipcc", *FLAGS, *extra, *objs, "-o", built], capture_output=True, text=True)
+            outs.append(res.stdout + res.stderr)
+            rc.append(res.returncode)
+        noise = ("packed-fp32-ops", "kernel-resource-usage")
+        msgs = [ln for ln in "\n".join(outs).splitlines()
+                if not any(n in ln for n in noise) and ln.strip() and not ln.startswith(" ") and ln.strip() != "^"]
+        if any(rc):
+            raise RuntimeError("hipcc failed:\n" + "\n".join(msgs))
+        if verbose and msgs:
+            print("\n".join(msgs))
+        check_resources(resource_usage("\n".join(outs)))
+        if not sanitize:  # (the same device code)
+            hazards.check(built)
+        shutil.copy(built, lib + ".tmp")
+    os.replace(lib + ".tmp", lib)
     return lib
 
 
