@@ -1386,10 +1386,11 @@ __global__ void reset_counters(unsigned int* __restrict__ c, int n) {
 }
 
 // ---------------------------------------------------------------------------
-// Weighting, update and best tracking.  Grid (the most parts of the launch's
-// instances, instances): the workgroups of an instance each take one slice of
-// its samples (U.parts of them, update_parts(N)); the workgroups beyond that
-// return at once.
+// Weighting, update and best tracking.  Grid (the most workgroups of one of the
+// launch's instances, instances): an instance's workgroups each take one slice of
+// its samples (U.parts of them, update_shape(N)), where samples are drawn again and
+// the launch says so (`tile`) one share of the slice's element blocks; the workgroups
+// beyond that return at once.
 // out (per call): the final nominal, best knots and info of the last iteration.
 // ---------------------------------------------------------------------------
 
@@ -1416,7 +1417,7 @@ template <int T>
 __device__ __forceinline__ float block_sum(float x, float* buf) {
   const int t = threadIdx.x;
   if constexpr (T > 64) {
-    if (t < T) buf[t] = x;
+    buf[t] = x;
     __syncthreads();
 #pragma unroll
     for (int off = T / 2; off > 64; off >>= 1) {
@@ -1425,7 +1426,7 @@ __device__ __forceinline__ float block_sum(float x, float* buf) {
     }
     if (t < 64) x = buf[t] + buf[t + 64];
   }
-  if (t < 64) {
+  if (T == 64 || t < 64) {
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) x += __shfl_down(x, off, 64);  // lanes < off hold the tree's sums
     if (t == 0) buf[T] = x;
@@ -1436,7 +1437,12 @@ __device__ __forceinline__ float block_sum(float x, float* buf) {
 
 // A part's sums are read by the workgroup that finishes last, on any XCD: stored
 // through to memory (agent scope), so that publishing them takes a wait for the
-// stores and no fence, which would write back the XCD's whole L2.
+// stores and no release, which would write back the XCD's whole L2.  This rests on
+// gfx950, not on the language's memory model (which wants that release before the
+// counter): an agent-scope store carries sc1, is written through its XCD's L2 to the
+// memory that all XCDs share and counts down vmcnt only there; the counters' atomics
+// are performed there too, after that wait; and the reader's fence drops its own
+// XCD's stale lines (buffer_inv sc1) before it reads.
 __device__ __forceinline__ void store_agent(float* p, float v) {
   __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
