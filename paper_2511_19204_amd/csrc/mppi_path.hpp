@@ -388,6 +388,7 @@ struct PathJoint {
 
 // backward_joint: from the articulated inertia I of body F to its joint terms and
 // the inertia O carried to the parent's origin.
+template <bool FB>
 __device__ __forceinline__ void path_backward(const PathInertia& I, const PathFrame& F, int k, float tau, float arm,
                                               float gain, PathJoint& J, PathInertia& O) {
   const Rep3 ax = rep3(F.ax);
@@ -406,6 +407,11 @@ __device__ __forceinline__ void path_backward(const PathInertia& I, const PathFr
         "v"(I.pa));
   const float Dv = (arm + gain) + d;
   J.invD = rcp(Dv);
+  // Beside a floating base the difference stays behind the reciprocal, whose wait it
+  // fills (quadruped, 256 x 200 steps: 625 us, 631 with the compiler's s_nop there); a
+  // fixed base is faster as the compiler orders it (branching arm 825 us, 837).
+  // Memory and scalar instructions may cross.
+  if constexpr (FB) __builtin_amdgcn_sched_barrier(0x94);
   J.u = tau - s;
   const float Wl = J.Ul * J.invD;
   // uD = u / D and Wa = Ua / D (plain reads, before those through DPP), then
@@ -873,7 +879,7 @@ __device__ __attribute__((always_inline)) void path_item(const DevInst& I, int f
       }
       const float ti = i % 3 == 0 ? quad_of<0>(tau[s]) : (i % 3 == 1 ? quad_of<1>(tau[s]) : quad_of<2>(tau[s]));
       const float gi = i % 3 == 0 ? quad_of<0>(gain[s]) : (i % 3 == 1 ? quad_of<1>(gain[s]) : quad_of<2>(gain[s]));
-      path_backward(IA, Fr[i], k, ti, arm[i], gi, J[i], Ip);
+      path_backward<FB>(IA, Fr[i], k, ti, arm[i], gi, J[i], Ip);
     }
 
     // ---- root: the base's articulated inertia and its solve, on every lane
