@@ -176,9 +176,10 @@ mppi_status mppi_get_tick(const mppi_ctx* c, uint32_t* tick);
  *                        lanes per rollout = a power of two 4..64 >= n_bodies.
  *                        At the smallest such count, and where the tree has at
  *                        most 8 root-to-leaf paths of at most 6 bodies, launches
- *                        share a rollout by path instead (four lanes or one to
- *                        each path, by the size of the launch), bit for bit the
- *                        same; persistent launches keep one lane per body.
+ *                        share a rollout by path where that is the faster (four
+ *                        lanes or one to each path, by the tree and the size of the
+ *                        launch), bit for bit the same; persistent launches keep one
+ *                        lane per body.
  *   MPPI_SCHEDULE_CHAIN  one lane per kinematic chain of the tree's heavy-path
  *                        decomposition (a body continues its parent's chain when
  *                        it heads the parent's largest subtree); each lane walks
@@ -388,8 +389,9 @@ mppi_status mppi_debug_rollouts(mppi_ctx* c, const float* d_state, const float* 
                                 uint32_t* d_masks, void* stream);
 
 /* Step-by-step record of iteration `iter` of mppi_step at noise tick `tick`,
- * from d_state and the nominal d_knots_in, with mppi_step's own rollout kernel
- * and launch shape (the simulate step of Alg. 1 with the Sec. IV-A costs):
+ * from d_state and the nominal d_knots_in, with the body schedule's rollout kernel
+ * of one lane per body, whose results are those of mppi_step bit for bit (the
+ * simulate step of Alg. 1 with the Sec. IV-A costs):
  *   d_trace_map [N] device int32, record slot of sample n or -1 (not recorded)
  *   d_trace     [slots][H + 1][nq + 2 nv + 2] device float: record h < H holds
  *               the state (q, v) at the start of control step h, the

@@ -1875,7 +1875,7 @@ extern "C" mppi_status mppi_debug_rollouts(mppi_ctx* c, const float* d_state, co
 }
 
 // The traced twin of launch_rollout for one instance of the body schedule: the
-// same grid, block, LDS layout and depth specialisation as mppi_step's launch.
+// same grid, block, LDS layout and depth specialisation as the body kernel's launch.
 template <int G>
 static hipError_t launch_trace_G(const DevInst* inst, int N, const LaunchShape& sh, const Dims& dm, hipStream_t s) {
   const int blocks = (N + sh.groups - 1) / sh.groups;

@@ -14,8 +14,12 @@ constexpr int kMaxChains = 8;    // chain schedule: kinematic chains (lanes) per
 constexpr int kMaxLevels = 16;   // chain schedule: tree depth + 1
 constexpr int kRow = 68;         // floats per body row of the chain schedule's table
 constexpr int kCt = 8;           // floats per contact row of that table
-constexpr int kMaxPaths = 8;     // path kernels: root-to-leaf paths (quads of lanes) per rollout
-constexpr int kMaxPath = 6;      // path kernels: bodies of a path
+// Path kernels: root-to-leaf paths (quads of lanes) per rollout, bodies of a path.  A
+// seventh body does not fit: the kernel holds a path's frames and joint terms in
+// registers, 483 of the 512 with six bodies, and spills 148 bytes a lane with seven.
+// Nine paths would take all 64 lanes for one rollout in the quad form.
+constexpr int kMaxPaths = 8;
+constexpr int kMaxPath = 6;
 constexpr int kPathRow = 28;     // floats per path, body and coordinate lane of their constants
 constexpr int kLaneRow = 52;     // floats per path and body of the constants of their one-lane form
 constexpr int kLaneExch = 28;    // floats per lane of its exchange records

@@ -634,8 +634,7 @@ __device__ __forceinline__ float from_first_quad(float x) {
 // 256 the vector instructions address hold them (a fixed-base arm of three
 // bodies); beside a floating base's state the inertias are read from LDS at each
 // use (in registers they would be fetched back from the accumulation file: 59
-// moves a step, 0.653 -> 0.644 ms at 256 x 200 steps of the quadruped), and so are
-// all constants of longer paths.
+// moves, 1.4 % of the quadruped's step), and so are all constants of longer paths.
 template <int G, int L, bool FB>
 __device__ __attribute__((always_inline)) void path_item(const DevInst& I, int first, float* smem, int steps,
                                                          float* state_out, const float* x0_in,
@@ -1026,7 +1025,7 @@ __device__ __attribute__((always_inline)) void path_item(const DevInst& I, int f
   wave_sync();
 }
 
-// The item function of an instance's tree (path_key in mppi_api.hip offers the
+// The item function of an instance's tree (path_fits in mppi_api.hip offers the
 // kernels only trees that one of these holds).
 template <int L, bool FB>
 __device__ __forceinline__ void path_item_of(const DevInst& I, int first, float* smem, int steps, float* state_out,
